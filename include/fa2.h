@@ -22,6 +22,8 @@
 #ifndef FA2_H_
 #define FA2_H_
 
+#include <stddef.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -135,10 +137,29 @@ int fa2_fwd_qk(const void* Q, const void* K, const void* V, void* O, float* LSE,
                float scale, int dtype, int mask, void* stream);
 
 /*
+ * fa2_fwd_ws -- fa2_fwd_qk with scratch memory.  When a problem has too few query tiles to fill the chip (a decoding
+ * step, a few queries against many keys) its keys are split over workgroups, which leave partial results in
+ * fp32 in `workspace`; a second kernel on the same stream merges them.  The function computed is the same.
+ *
+ *  workspace     device, 16-byte aligned, `workspace_bytes` bytes of any content; owned by the caller, overwritten,
+ *                and free for other use once the stream has run the call.  Calls that may run at the same time need
+ *                one each.  With NULL, or less than fa2_workspace_bytes() of it, the keys are not split: the call
+ *                is then exactly fa2_fwd_qk.
+ *
+ * fa2_workspace_bytes -- what fa2_fwd_ws can use for a problem: 0 when its keys are not split (and for sizes, head
+ * dimensions or masks that the entry points refuse).  Host only.  Always 0 below FA2_SPLIT_MIN_KEYS keys.
+ */
+enum { FA2_SPLIT_MIN_KEYS = 512 };
+int fa2_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int H, int Nq, int Nk, int d,
+               float scale, int dtype, int mask, void* workspace, size_t workspace_bytes, void* stream);
+size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int mask);
+
+/*
  * fa2_tile_shape -- which tile shape (FA2_VARIANT_NARROW or FA2_VARIANT_NARROW8) the entry points without a
  * `variant` argument use for a problem; the counterpart of reading the best cell off the paper's Table 1.  Host
  * only: nothing is launched and no HIP call is made.  Returns the FA2_VARIANT_* value (> 0), or a negative
- * FA2_ERR_* for sizes, head dimensions or masks that the entry points refuse.
+ * FA2_ERR_* for sizes, head dimensions or masks that the entry points refuse.  (A single query row, Nq == 1, runs in
+ * a kernel of its own that has no query tiles; the value returned is the tile shape it would otherwise get.)
  */
 int fa2_tile_shape(int B, int H, int Nq, int Nk, int d, int mask);
 

@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from contextlib import nullcontext
 
 FA2_FP16 = 0
 FA2_BF16 = 1
@@ -19,6 +20,7 @@ FA2_VARIANT_NARROW = 1
 FA2_VARIANT_NARROW8 = 3
 FA2_MASK_NONE = 0
 FA2_MASK_CAUSAL = 1
+FA2_SPLIT_MIN_KEYS = 512
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libfa2.so")
@@ -55,6 +57,10 @@ def load_library():
         lib.fa2_fwd_masked.restype = ci
         lib.fa2_fwd_qk.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ctypes.c_float, ci, ci, vp]
         lib.fa2_fwd_qk.restype = ci
+        lib.fa2_fwd_ws.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ctypes.c_float, ci, ci, vp, ctypes.c_size_t, vp]
+        lib.fa2_fwd_ws.restype = ci
+        lib.fa2_workspace_bytes.argtypes = [ci, ci, ci, ci, ci, ci]
+        lib.fa2_workspace_bytes.restype = ctypes.c_size_t
         lib.fa2_strerror.argtypes = [ci]
         lib.fa2_strerror.restype = ctypes.c_char_p
         lib.fa2_tile_shape.argtypes = [ci, ci, ci, ci, ci, ci]
@@ -130,6 +136,19 @@ def fa2_fwd_qk_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, Nq, Nk, d, scale, 
                                          float(scale), int(dtype), int(mask), stream))
 
 
+def fa2_workspace_bytes(B: int, H: int, Nq: int, Nk: int, d: int, mask: int = FA2_MASK_NONE) -> int:
+    """Bytes of scratch memory that ``fa2_fwd_ws`` can use for a problem (0: its keys are not split).  No launch."""
+    return int(load_library().fa2_workspace_bytes(int(B), int(H), int(Nq), int(Nk), int(d), int(mask)))
+
+
+def fa2_fwd_ws_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, Nq, Nk, d, scale, dtype, mask, workspace_ptr,
+                   workspace_bytes, stream=None) -> int:
+    """Call ``fa2_fwd_ws`` (``fa2_fwd_qk`` with scratch memory) with raw device addresses; returns the C code."""
+    return int(load_library().fa2_fwd_ws(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, int(B), int(H), int(Nq), int(Nk), int(d),
+                                         float(scale), int(dtype), int(mask), workspace_ptr, int(workspace_bytes),
+                                         stream))
+
+
 def _launch(torch, q, k, v, out, lse, scale, dtype, stream, variant, causal) -> int:
     """The call into the library for checked tensors of the current device; returns the C return code.
 
@@ -145,9 +164,19 @@ def _launch(torch, q, k, v, out, lse, scale, dtype, stream, variant, causal) -> 
         return fa2_fwd_variant_raw(*ptrs, B, H, N, d, scale, dtype, variant, handle)
     lib = load_library()
     mask = FA2_MASK_CAUSAL if causal else FA2_MASK_NONE
-    if Nk != N:
-        return lib.fa2_fwd_qk(*ptrs, B, H, N, Nk, d, float(scale), dtype, mask, handle)
-    return lib.fa2_fwd_masked(*ptrs, B, H, N, d, float(scale), dtype, mask, handle)
+    workspace, nbytes = None, 0
+    if Nk >= FA2_SPLIT_MIN_KEYS and (stream is None or isinstance(stream, torch.cuda.Stream)):
+        nbytes = lib.fa2_workspace_bytes(B, H, N, Nk, d, mask)
+        if nbytes:
+            # Scratch that belongs to the launch stream: dropped on return, its memory is handed out again only behind
+            # this call's kernels.  Without it the call still runs, its keys unsplit.
+            try:
+                with nullcontext() if stream is None else torch.cuda.stream(stream):
+                    workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
+            except torch.cuda.OutOfMemoryError:
+                pass
+    return lib.fa2_fwd_ws(*ptrs, B, H, N, Nk, d, float(scale), dtype, mask,
+                          None if workspace is None else workspace.data_ptr(), nbytes, handle)
 
 
 def fa2_fwd(q, k, v, scale: float, out=None, lse=None, return_lse: bool = True, stream=None,

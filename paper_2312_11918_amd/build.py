@@ -7,7 +7,8 @@ import subprocess
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
-SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]
+SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile kernels and the C ABI
+SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip")]       # one query per sequence, keys split
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
 PROBE_SOURCES = [os.path.join(_PKG, "csrc", "mfma_probe.hip")]
@@ -35,26 +36,29 @@ def _hipcc(sources, library, verbose):
 def build_library(verbose: bool = False) -> str:
     """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
-    return _hipcc(SOURCES, LIBRARY, verbose)
+    return _hipcc([*SOURCES, *SPLIT_SOURCES], LIBRARY, verbose)
 
 
-def resource_usage():
-    """Compile the attention kernels for the device only and return what the compiler reports per kernel: a list
+def resource_usage(sources=SOURCES):
+    """Compile the kernels of `sources` for the device only and return what the compiler reports per kernel: a list
     of dicts with the (demangled) kernel name, VGPRs, AGPRs, SGPRs, scratch bytes per lane, LDS bytes per workgroup
     and wavefronts per SIMD.  Nothing is written; used by the test that keeps every kernel free of scratch."""
     import re
 
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
-    cmd = [hipcc, *flags, "-I", INCLUDE, "--cuda-device-only", "-c", "-o", os.devnull,
-           "-Rpass-analysis=kernel-resource-usage", *SOURCES]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+    report = ""
+    for source in sources:
+        cmd = [hipcc, *flags, "-I", INCLUDE, "--cuda-device-only", "-c", "-o", os.devnull,
+               "-Rpass-analysis=kernel-resource-usage", source]
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout)
+        report += res.stdout
     keys = {"TotalSGPRs": "sgprs", "VGPRs": "vgprs", "AGPRs": "agprs", "ScratchSize [bytes/lane]": "scratch_bytes_per_lane",
             "Occupancy [waves/SIMD]": "waves_per_simd", "LDS Size [bytes/block]": "lds_bytes_per_workgroup"}
     kernels, cur = [], None
-    for line in res.stdout.splitlines():
+    for line in report.splitlines():
         m = re.search(r"remark:\s+(.*?)\s+\[-Rpass-analysis", line)
         if not m:
             continue

@@ -22,11 +22,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <tuple>
 #include <type_traits>
 #include <utility>
 
-#include "fa2.h"
+#include "fa2_internal.h"
+
+using fa2::enqueue;
+using fa2::kCUs;
 
 namespace {
 
@@ -43,7 +45,6 @@ constexpr int kWaves = 4;            // wavefronts per workgroup of the 128-row 
 constexpr int kBr = 32 * kWaves;     // query rows per workgroup (32 per wavefront)
 constexpr int kBc = 64;              // keys per K/V tile
 constexpr int kSpinLimit = 1 << 18;  // polls of the arrival count before a wavefront gives up (tens of milliseconds)
-constexpr int kCUs = 256;            // compute units of the whole chip (tile-shape choice only)
 constexpr int kXcds = 8;             // accelerator complex dies; workgroup i is dispatched to XCD i % 8
 constexpr float kLazyLog2 = 8.0f;    // the rowmax reference moves only when exceeded by 2^8
 
@@ -773,17 +774,6 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
 
 constexpr int kRows256 = 256;  // query rows per workgroup of the 8-wavefront shape
 
-// Enqueues `kernel` and reports this launch's own status (not whatever error an earlier, unrelated HIP call left).
-template <class... Params, class... Args>
-int enqueue(void (*kernel)(Params...), int grid, int block, hipStream_t stream, Args... args) {
-  std::tuple<Params...> values{static_cast<Params>(args)...};
-  void* ptrs[sizeof...(Params)];
-  std::apply([&](auto&... v) { int i = 0; ((ptrs[i++] = &v), ...); }, values);
-  const hipError_t err = hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)grid), dim3((unsigned)block),
-                                         ptrs, 0, stream);
-  return err == hipSuccess ? FA2_OK : FA2_ERR_LAUNCH;
-}
-
 // One instantiation of the 32-row kernel.
 template <int DT, int D, int kWv, int kNBuf, bool kCausal, bool kRagged>
 int launch_rows32(const void* Q, const void* K, const void* V, void* O, float* LSE, int H, int Nq, int Nk,
@@ -858,7 +848,7 @@ int choose_variant(int B, int H, int Nq, int Nk, int d, int mask) {
 }
 
 int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int H, int Nq, int Nk, int d,
-        float scale, int dtype, int variant, int mask, void* stream) {
+        float scale, int dtype, int variant, int mask, void* stream, void* workspace = nullptr, size_t workspace_bytes = 0) {
   // All validation happens before the first HIP call: an error launches nothing.
   if (Q == nullptr || K == nullptr || V == nullptr || O == nullptr) return FA2_ERR_INVALID_ARG;
   if (B <= 0 || H <= 0 || Nq <= 0 || Nk <= 0 || d <= 0) return FA2_ERR_INVALID_ARG;
@@ -877,6 +867,11 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
   // the K/V rows of one batch entry are addressed with 32-bit byte offsets from a buffer descriptor
   if ((unsigned long long)n_max * (unsigned long long)H * (unsigned long long)d * 2ull >= (1ull << 32))
     return FA2_ERR_UNSUPPORTED;
+  if (variant == FA2_VARIANT_AUTO && fa2::decode_accepts(B, H, Nq)) {
+    return fa2::decode(fa2::Problem{Q, K, V, O, LSE, B, H, Nq, Nk, d, scale * 1.44269504088896340736f, dtype,
+                                    mask == FA2_MASK_CAUSAL, static_cast<hipStream_t>(stream)},
+                       workspace, workspace_bytes);
+  }
   if (variant == FA2_VARIANT_AUTO) variant = choose_variant(B, H, Nq, Nk, d, mask);
   if (variant != FA2_VARIANT_NARROW) {
     // the 256-row shape: whole tiles, square, d <= 128
@@ -913,6 +908,17 @@ extern "C" int fa2_fwd_qk(const void* Q, const void* K, const void* V, void* O, 
 extern "C" int fa2_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int H, int N, int d,
                        float scale, int dtype, void* stream) {
   return run(Q, K, V, O, LSE, B, H, N, N, d, scale, dtype, FA2_VARIANT_AUTO, FA2_MASK_NONE, stream);
+}
+
+extern "C" int fa2_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int H, int Nq, int Nk,
+                          int d, float scale, int dtype, int mask, void* workspace, size_t workspace_bytes, void* stream) {
+  if (!aligned(workspace, 16)) return FA2_ERR_INVALID_ARG;
+  return run(Q, K, V, O, LSE, B, H, Nq, Nk, d, scale, dtype, FA2_VARIANT_AUTO, mask, stream, workspace, workspace_bytes);
+}
+
+extern "C" size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int mask) {
+  if (fa2_tile_shape(B, H, Nq, Nk, d, mask) < 0) return 0;
+  return fa2::decode_accepts(B, H, Nq) ? fa2::decode_workspace(B, H, Nk, d) : 0;
 }
 
 extern "C" int fa2_tile_shape(int B, int H, int Nq, int Nk, int d, int mask) {

@@ -1,0 +1,45 @@
+// What the translation units of libfa2 share: the validated problem and the launchers beside the tile kernels.
+#ifndef FA2_INTERNAL_H_
+#define FA2_INTERNAL_H_
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <tuple>
+
+#include "fa2.h"
+
+namespace fa2 {
+
+constexpr int kCUs = 256;  // compute units of the whole chip (choice of tile shapes and of key splits)
+
+// A problem that has passed validation.
+struct Problem {
+  const void *Q, *K, *V;
+  void* O;
+  float* LSE;  // may be null
+  int B, H, Nq, Nk, d;
+  float scale_log2e;  // scale * log2(e)
+  int dtype;
+  bool causal;
+  hipStream_t stream;
+};
+
+// Enqueues `kernel` and reports this launch's own status (not whatever error an earlier, unrelated HIP call left).
+template <class... Params, class... Args>
+int enqueue(void (*kernel)(Params...), int grid, int block, hipStream_t stream, Args... args) {
+  std::tuple<Params...> values{static_cast<Params>(args)...};
+  void* ptrs[sizeof...(Params)];
+  std::apply([&](auto&... v) { int i = 0; ((ptrs[i++] = &v), ...); }, values);
+  const hipError_t err = hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)grid), dim3((unsigned)block),
+                                         ptrs, 0, stream);
+  return err == hipSuccess ? FA2_OK : FA2_ERR_LAUNCH;
+}
+
+// fa2_decode.hip: one query per sequence (Nq == 1).  The workspace is used only if it holds decode_workspace bytes.
+__attribute__((visibility("hidden"))) bool decode_accepts(int B, int H, int Nq);
+__attribute__((visibility("hidden"))) size_t decode_workspace(int B, int H, int Nk, int d);
+__attribute__((visibility("hidden"))) int decode(const Problem& p, void* workspace, size_t workspace_bytes);
+
+}  // namespace fa2
+#endif  // FA2_INTERNAL_H_

@@ -1,0 +1,69 @@
+"""GPU parity of the single-query kernel (Nq == 1) against the fp64 CPU oracle: key counts around its step sizes and its
+splits, with the keys split (workspace) and unsplit (none).  P and O are held in fp32 until O is rounded once, so O may
+be off by half an ulp of the 16-bit type (2^-11 / 2^-8 relative) plus fp32 sums: checked as |dO| <= |O| ulp/2 + 1e-5."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2312_11918_amd as fa2
+from test_gpu_ragged import PAD, SENT16, SENT32, _guarded, _make
+from _gpu_common import torch_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _decode(qb, kb, vb, dtype, scale, split):
+    torch = torch_gpu()
+    B, _, H, d = qb.shape
+    Nk = kb.shape[1]
+    q, k, v = (_guarded(x, dtype)[0] for x in (qb, kb, vb))
+    o, o_whole = _guarded(np.full(qb.shape, SENT16, dtype=np.uint16), dtype)
+    lse_whole = torch.full((B * H + 2 * PAD,), float(SENT32), dtype=torch.float32, device="cuda")
+    lse = lse_whole[PAD:PAD + B * H].view(B, H, 1)
+    if split:
+        fa2.fa2_fwd(q, k, v, scale, out=o, lse=lse)
+    else:
+        rc = fa2.fa2_fwd_qk_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, 1, Nk, d, scale,
+                                fa2.FA2_FP16 if dtype == "fp16" else fa2.FA2_BF16, fa2.FA2_MASK_NONE,
+                                torch.cuda.current_stream().cuda_stream)
+        assert rc == fa2.FA2_OK
+    torch.cuda.synchronize()
+    ow, lw = o_whole.cpu().numpy().view(np.uint16), lse_whole.cpu().numpy()
+    assert np.all(ow[:PAD] == SENT16) and np.all(ow[PAD + qb.size:] == SENT16), "O was written outside its bounds"
+    assert np.all(lw[:PAD] == SENT32) and np.all(lw[PAD + B * H:] == SENT32), "LSE was written outside its bounds"
+    return o.double().cpu().numpy(), lse.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("B,H,Nk,d,dtype,outliers", [
+    (1, 1, 1, 64, "fp16", 0.0),          # one key: O = V_0
+    (2, 3, 7, 256, "bf16", 0.0),         # d = 256: steps of 8 keys
+    (2, 3, 9, 256, "fp16", 0.0),
+    (1, 2, 16, 128, "bf16", 0.0),        # steps of 16
+    (1, 2, 17, 128, "fp16", 0.0),
+    (3, 1, 31, 64, "bf16", 0.0),         # steps of 32
+    (3, 2, 33, 64, "fp16", 0.02),
+    (2, 5, 257, 128, "fp16", 0.0),       # one key past what sixteen wavefronts take in a step
+    (33, 8, 300, 64, "bf16", 0.0),       # more heads than CUs
+    (70, 8, 513, 128, "fp16", 0.0),      # ... and than twice the CUs
+    (1, 2, 2047, 64, "fp16", 0.0),       # the last length that is not split at d = 64
+    (1, 2, 2048, 64, "bf16", 0.0),       # the first that is
+    (1, 2, 1024, 128, "bf16", 0.0),      # the first at d = 128: a step of keys per wavefront
+    (1, 1, 513, 256, "fp16", 0.01),
+    (13, 10, 1100, 128, "fp16", 0.0),    # 130 heads: several rounds of workgroups
+    (12, 24, 1024, 128, "bf16", 0.0),    # 288 heads, split as well
+    (3, 7, 5001, 128, "fp16", 0.01),     # uneven splits
+    (1, 32, 16001, 64, "fp16", 0.0),
+    (2, 16, 32768, 128, "bf16", 0.0),
+])
+@pytest.mark.parametrize("split", [True, False])
+def test_single_query_parity(B, H, Nk, d, dtype, outliers, split):
+    print(f"decode B={B} H={H} Nk={Nk} d={d} {dtype} split={split}", flush=True)
+    qb, kb, vb = _make(B, H, 1, Nk, d, dtype, 5000 + Nk + d, outliers)
+    scale = float(np.float32(d) ** np.float32(-0.5))
+    torch_gpu()   # torch first: libfa2 then finds the HIP runtime that torch has loaded
+    assert (fa2.fa2_workspace_bytes(B, H, 1, Nk, d) > 0) == (Nk * d >= 128 * 1024 and B * H < 512)
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale)
+    o, lse = _decode(qb, kb, vb, dtype, scale, split)
+    half_ulp = 2.0 ** (-11 if dtype == "fp16" else -8)
+    assert np.all(np.abs(o - o_ref) <= np.abs(o_ref) * half_ulp + 1e-5)
+    assert np.all(np.abs(lse - lse_ref) <= 1e-5 * np.maximum(1.0, np.abs(lse_ref)))

@@ -1,0 +1,32 @@
+"""Host logic and compiled form of the kernels that split the keys (no GPU): registers, and the scratch memory asked for."""
+import pytest
+
+import paper_2312_11918_amd as fa2
+from paper_2312_11918_amd import build
+
+
+def test_no_split_kernel_uses_scratch_memory():
+    kernels = build.resource_usage(build.SPLIT_SOURCES)
+    assert kernels
+    bad = [(k["name"], k["scratch_bytes_per_lane"]) for k in kernels if k["scratch_bytes_per_lane"] != 0]
+    assert not bad, f"kernels that spill to scratch: {bad}"
+
+
+@pytest.mark.parametrize("B,H,Nk,d,splits", [
+    (1, 32, 16001, 64, 8),      # 32 heads: one round of 256 workgroups
+    (3, 12, 30000, 64, 7),      # 36 heads: 252
+    (1, 1, 513, 256, 8),        # no more than a step of keys per wavefront
+    (12, 24, 1500, 128, 4),     # 288 heads, 1.1 rounds: 4.5 rounds
+    (16, 16, 2048, 128, 1),     # the heads fill the CUs
+    (1, 32, 1023, 128, 1),      # too few keys
+])
+def test_decode_splits(B, H, Nk, d, splits):
+    want = 0 if splits == 1 else B * H * splits * (d + 2) * 4   # O, maximum and sum in fp32 per split
+    assert fa2.fa2_workspace_bytes(B, H, 1, Nk, d) == want
+
+
+def test_workspace_of_refused_problems_is_zero():
+    assert fa2.fa2_workspace_bytes(1, 1, 1, 4096, 96) == 0
+    assert fa2.fa2_workspace_bytes(0, 1, 1, 4096, 64) == 0
+    assert fa2.fa2_workspace_bytes(1, 1, 1, 4096, 64, fa2.FA2_MASK_CAUSAL) == 0
+    assert fa2.fa2_fwd_ws_raw(4096, 4096, 4096, 4096, None, 1, 1, 1, 4096, 64, 0.125, 0, 0, 4104, 1 << 20) == fa2.FA2_ERR_INVALID_ARG
