@@ -8,7 +8,8 @@ import subprocess
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile kernels and the C ABI
-SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip")]       # one query per sequence, keys split
+SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query per sequence, keys split
+                 os.path.join(_PKG, "csrc", "fa2_split.hip")]        # few query tiles, keys split
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
 PROBE_SOURCES = [os.path.join(_PKG, "csrc", "mfma_probe.hip")]

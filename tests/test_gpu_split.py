@@ -1,0 +1,86 @@
+"""GPU parity of the launches that cut the keys (few Q tiles): halves inside a workgroup, slices over workgroups and their
+merge, against the fp64 CPU oracle on guarded buffers, with the tolerances of the whole launches."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2312_11918_amd as fa2
+from test_gpu_ragged import _check, _guarded, _make, _run
+from _gpu_common import torch_gpu
+
+pytestmark = pytest.mark.gpu
+
+# B, H, Nq, Nk, d, dtype, causal, outliers, sliced: sizes at the edges of a half (64 keys), a step of both (128), the padding
+# to four tiles, and a slice; the last slice with one tile, with a part of one; Q tiles with dead wavefronts
+CASES = [
+    (1, 2, 129, 1500, 128, "fp16", False, 0.0, True),
+    (1, 2, 128, 641, 128, "bf16", False, 0.0, False),     # 12 tiles, the last pair with one key
+    (2, 3, 100, 2000, 64, "fp16", False, 0.02, True),
+    (1, 8, 33, 4097, 128, "bf16", False, 0.0, True),     # slices; the last one starts the last pair of tiles
+    (1, 1, 2, 16384, 64, "fp16", False, 0.0, True),
+    (1, 1, 31, 5000, 256, "bf16", False, 0.0, True),
+    (1, 4, 300, 3000, 256, "fp16", False, 0.01, True),
+    (2, 8, 1024, 1024, 128, "fp16", False, 0.0, False),  # halves only
+    (2, 24, 200, 1500, 64, "bf16", False, 0.0, False),
+    (1, 16, 1111, 1111, 128, "bf16", True, 0.0, False),
+    (2, 2, 321, 321, 64, "fp16", True, 0.0, False),
+    (1, 6, 3000, 3000, 128, "fp16", True, 0.01, True),   # causal slices: the first Q tiles lie in one slice
+    (1, 3, 1500, 1500, 64, "bf16", True, 0.0, True),
+    (1, 2, 1409, 1409, 256, "fp16", True, 0.0, True),    # a last Q tile of one row
+    (1, 2, 640, 640, 128, "fp16", True, 0.0, False),
+]
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d,dtype,causal,outliers,sliced", CASES)
+def test_split_parity(B, H, Nq, Nk, d, dtype, causal, outliers, sliced):
+    print(f"split case B={B} H={H} Nq={Nq} Nk={Nk} d={d} {dtype} causal={causal}", flush=True)
+    torch = torch_gpu()
+    mask = fa2.FA2_MASK_CAUSAL if causal else fa2.FA2_MASK_NONE
+    assert (fa2.fa2_workspace_bytes(B, H, Nq, Nk, d, mask) > 0) == sliced
+    qb, kb, vb = _make(B, H, Nq, Nk, d, dtype, 31000 + Nq + Nk + d, outliers)
+    scale = float(np.float32(d) ** np.float32(-0.5))
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale, causal=causal)
+    o, lse = _run(qb, kb, vb, dtype, scale, causal)
+    _check(o, lse, o_ref, lse_ref, "with a workspace")
+    # the same problem through the C ABI without a workspace, and with one that is too small
+    q, k, v = (_guarded(x, dtype)[0] for x in (qb, kb, vb))
+    small = torch.full((1024,), 255, dtype=torch.uint8, device="cuda")
+    for ws, n in ((None, 0), (small.data_ptr(), 512)):
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((B, H, Nq), float("nan"), dtype=torch.float32, device="cuda")
+        rc = fa2.fa2_fwd_ws_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, Nq, Nk, d,
+                                scale, fa2.FA2_FP16 if dtype == "fp16" else fa2.FA2_BF16, mask, ws, n,
+                                torch.cuda.current_stream().cuda_stream)
+        assert rc == fa2.FA2_OK
+        torch.cuda.synchronize()
+        _check(o.double().cpu().numpy(), lse.double().cpu().numpy(), o_ref, lse_ref, "without")
+    assert bool((small == 255).all())
+
+
+@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128)])
+def test_split_on_another_stream_and_in_a_graph(Nq, Nk, d):
+    # the workspace belongs to the launch stream, or to the graph's pool: bits as on the current stream
+    torch = torch_gpu()
+    print(f"split stream/graph Nq={Nq} Nk={Nk}", flush=True)
+    assert fa2.fa2_workspace_bytes(1, 8, Nq, Nk, d) > 0
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, n, 8, d), generator=g, device="cuda").half() for n in (Nq, Nk, Nk))
+    ref, ref_lse = fa2.fa2_fwd(q, k, v, d ** -0.5)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    outs = []
+    for _ in range(5):
+        o, lse = fa2.fa2_fwd(q, k, v, d ** -0.5, out=torch.empty_like(q), lse=torch.empty_like(ref_lse), stream=side)
+        outs.append((o, lse))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref) and torch.equal(x, ref_lse) for o, x in outs)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o, lse = fa2.fa2_fwd(q, k, v, d ** -0.5)
+    for _ in range(4):
+        o.fill_(float("nan"))
+        lse.fill_(float("nan"))
+        junk = torch.full((1 << 22,), 3.0, device="cuda")   # the program's own work between replays
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, ref) and torch.equal(lse, ref_lse) and bool((junk == 3.0).all())
