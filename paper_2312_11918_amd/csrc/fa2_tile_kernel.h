@@ -266,14 +266,21 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
   // one head, n_qtiles-1-p and then p, one after the other: every workgroup then does the same amount of
   // work (but for the unpaired middle tile when n_qtiles is odd).  total_tiles counts pairs in that case.
   const int n_items = kSplit ? split.items : kCausal ? (n_qtiles + 1) / 2 : n_qtiles;
-  int bh = tile / n_items;                // batch entry * H + head (kChain: of the current pass)
-  const int item = tile - bh * n_items;   // Q tile, or pair of Q tiles (kChain: first Q tile)
+  int bh = tile / n_items;           // batch entry * H + head (kChain: of the current pass)
+  int item = tile - bh * n_items;    // Q tile, or pair of Q tiles (kChain: first Q tile)
+  if constexpr (kSplit && kCausal) {
+    // the items of a head differ in length: the longest of every head start first, so that the short ones fill the end
+    // (a number of heads that is a multiple of 8 still keeps each head on one XCD)
+    const int heads = total_tiles / n_items;
+    item = blockIdx.x / heads;
+    bh = blockIdx.x - item * heads;
+  }
   // passes of this workgroup: Q tiles it works through.  A chain longer than 1 under the causal mask is only
   // launched when every pair is complete (n_qtiles even).
   const int n_pass = kSplit ? 1 : kCausal ? (chain > 1 ? 2 * chain : item != n_qtiles - 1 - item ? 2 : 1) : kChain ? chain : 1;
   int qt, q_row, n_tiles;  // set per pass
   // kSplit: the items of a head run slice by slice, so that neighbouring workgroups read the same K and V.  Slice s
-  // concerns every Q tile, or under the causal mask those from its own first key on.
+  // concerns every Q tile, or under the causal mask those from its own first key on, the last Q tile first.
   int slice = 0, slice_qt = 0;
   if constexpr (kSplit) {
     int rest = item;
@@ -282,7 +289,7 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
       ++slice;
       if constexpr (kCausal) n -= split.chunk / 2;   // (a Q tile is two K/V tiles long)
     }
-    slice_qt = rest + (kCausal ? slice * (split.chunk / 2) : 0);
+    slice_qt = kCausal ? n_qtiles - 1 - rest : rest;
   }
   const int first_key = kSplit ? slice * split.chunk * kBc : 0;
   const int nk_all = Nk;   // keys of a batch entry in memory
@@ -778,10 +785,11 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
                         (!kRagged || tile_at(j + i) * kBc < Nk) && rows_live;
       // ... and only the tile that a wavefront's own rows cross, or that holds the last key, needs the mask and the row
       // maximum: the others of these tiles are wholly visible to it and take the unmasked tile's short path (not where
-      // kRowStores is off: no register left for the condition).  With the idle rescale left out as well: B8 H16 N2048
+      // kRowStores is off: no register left for the condition; nor at d = 256, which takes the maximum of every tile
+      // anyway and lost 3...5 % by it).  With the idle rescale left out as well: B8 H16 N2048
       // d128 bf16 causal 151.6 -> 148.5 us, N = 2047 unmasked 269.6 -> 267.7, the same bits.
       const int tile_end = (kCausal && !kSplit ? i : tile_at(j + i)) * kBc + kBc;   // first key past the tile
-      const bool straddles = !kRowStores || (!kCausal ? tile_end > Nk
+      const bool straddles = !kRowStores || D == 256 || (!kCausal ? tile_end > Nk
                                              : kSplit ? tile_end - 1 > qt * kRows + wave * 32 - first_key
                                                       : tile_end - 1 > wave * 32);
       if constexpr (i + 1 < kNBuf) {

@@ -28,6 +28,9 @@ CASES = [
     (1, 3, 1500, 1500, 64, "bf16", True, 0.0, True),
     (1, 2, 1409, 1409, 256, "fp16", True, 0.0, True),    # a last Q tile of one row
     (1, 2, 640, 640, 128, "fp16", True, 0.0, False),
+    (2, 24, 665, 665, 128, "bf16", True, 0.0, False),    # more Q tiles than CUs: longest first
+    (6, 16, 400, 400, 256, "fp16", True, 0.0, False),
+    (5, 11, 897, 897, 64, "fp16", True, 0.0, False),     # heads not a multiple of 8
 ]
 
 
