@@ -72,11 +72,16 @@ def resource_usage(sources=SOURCES):
             if k.strip() in keys:
                 cur[keys[k.strip()]] = int(v)
     for k in kernels:
-        m = re.search(r"fa2_fwd_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
+        m = re.search(r"fa2_fwd_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELb(\d)ELb(\d)E", k["mangled"])
         if m:
-            dt, d, wv, nbuf, causal, ragged = (int(x) for x in m.groups())
+            dt, d, wv, nbuf, causal, ragged, cut = (int(x) for x in m.groups())
             k["name"] = (f"fa2_fwd_kernel<{'fp16' if dt == 0 else 'bf16'}, d={d}, {wv} wavefronts, {nbuf} LDS buffers"
-                         f"{', causal' if causal else ''}{', partial tiles' if ragged else ''}>")
+                         f"{', causal' if causal else ''}{', partial tiles' if ragged else ''}{', keys cut' if cut else ''}>")
+            continue
+        m = re.search(r"(fa2_(?:decode|decode_merge|split_merge)_kernel)ILi(\d+)ELi(\d+)E(?:Lb(\d)E)?", k["mangled"])
+        if m:
+            flag = {None: "", "0": ""}.get(m[4], ", causal" if "split" in m[1] else ", keys split")
+            k["name"] = f"{m[1]}<{'fp16' if m[2] == '0' else 'bf16'}, d={m[3]}{flag}>"
         else:
             k["name"] = k["mangled"]
     return kernels
@@ -86,7 +91,7 @@ if __name__ == "__main__":
     import sys
 
     if "--resource-usage" in sys.argv:
-        rows = resource_usage()
+        rows = resource_usage([*SOURCES, *SPLIT_SOURCES])
         print("| kernel | VGPRs | AGPRs | SGPRs | scratch B/lane | LDS B/workgroup | wavefronts/SIMD |")
         print("|---|---|---|---|---|---|---|")
         for k in sorted(rows, key=lambda r: r["name"]):
