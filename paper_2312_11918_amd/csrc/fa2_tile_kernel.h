@@ -176,8 +176,11 @@ struct SplitArgs {
   int items = 0;             // workgroups per head
 };
 
+// Wavefronts per SIMD: at d = 64 the 4-wavefront kernels are held to 168 registers, three workgroups per CU.  With the
+// causal mask and partial tiles they took 195 before, two workgroups per CU: B50 H16 N330 fp16 56 -> 49 us, B60 H24 N140 fp16
+// 36.0 -> 31.6, B30 H8 N700 bf16 36.1 -> 32.8; whole tiles B40 H16 N384 bf16 42.0 -> 41.4, B8 H32 N2048 fp16 180 -> 178.
 template <int DT, int D, int kWv, int kNBuf, bool kCausal, bool kRagged, bool kSplit = false>
-__global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_fwd_kernel(
+__global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <= 128 ? 2 : 1) void fa2_fwd_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ LSE, int H, int Nq, int Nk, float scale_log2e, int n_qtiles,
     int total_tiles, int chain, SplitArgs split) {
@@ -335,8 +338,10 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
       lds_tile += half_lds;
     }
     // d = 256 with partial tiles has no registers to spare for sixteen loop-invariant source offsets: keep them
-    // from being hoisted out of the loop (they cost a few integer operations per load to recompute)
-    if constexpr (D == 256 && kRagged) asm volatile("" : "+v"(lane));
+    // from being hoisted out of the loop (they cost a few integer operations per load to recompute).  Nor has d = 64
+    // with the causal mask and partial tiles at three wavefronts per SIMD.  (At d = 128 the registers that this frees,
+    // 256 -> 230, would do for kRowStores, but the loop lost 6 % at N = 5000.)
+    if constexpr ((D == 256 || (D == 64 && kCausal)) && kRagged) asm volatile("" : "+v"(lane));
     if (kRagged && (j + 1) * kBc > Nk) {
       // a tile with rows past the last key: those rows are filled with copies of the last key's row, so LDS
       // holds finite numbers everywhere (their columns of S are masked; 0 * finite = 0 in GEMM-II)
@@ -786,10 +791,11 @@ __global__ __launch_bounds__(kWv * 64, (kWv == 4 && D <= 128) ? 2 : 1) void fa2_
       // ... and only the tile that a wavefront's own rows cross, or that holds the last key, needs the mask and the row
       // maximum: the others of these tiles are wholly visible to it and take the unmasked tile's short path (not where
       // kRowStores is off: no register left for the condition; nor at d = 256, which takes the maximum of every tile
-      // anyway and lost 3...5 % by it).  With the idle rescale left out as well: B8 H16 N2048
+      // anyway and lost 3...5 % by it, nor in the whole launches of d = 64 under the causal mask, where the registers it
+      // takes cost a workgroup per CU or 2 %).  With the idle rescale left out as well: B8 H16 N2048
       // d128 bf16 causal 151.6 -> 148.5 us, N = 2047 unmasked 269.6 -> 267.7, the same bits.
       const int tile_end = (kCausal && !kSplit ? i : tile_at(j + i)) * kBc + kBc;   // first key past the tile
-      const bool straddles = !kRowStores || D == 256 || (!kCausal ? tile_end > Nk
+      const bool straddles = !kRowStores || D == 256 || (D == 64 && kCausal && !kSplit) || (!kCausal ? tile_end > Nk
                                              : kSplit ? tile_end - 1 > qt * kRows + wave * 32 - first_key
                                                       : tile_end - 1 > wave * 32);
       if constexpr (i + 1 < kNBuf) {
