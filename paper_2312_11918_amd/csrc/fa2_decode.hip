@@ -23,6 +23,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLn2 = 0.69314718055994530942f;
+constexpr float kNoKey = -3.402823466e38f;   // reference point of a part that has seen no key (the lowest finite number)
 constexpr int kMaxWaves = 8;   // wavefronts per workgroup
 constexpr int kUnroll = 4;     // keys per lane group and step (8: 1...7 % slower, 2: 0...5 % slower)
 
@@ -59,13 +60,17 @@ template <int G> __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
-// exp2(a - b) for a merge, where a may be -inf (a part that saw no key) and b, the larger, is finite unless every part
-// is empty
-__device__ __forceinline__ float weight(float a, float b) { return a == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a - b); }
+// exp2(a - b) for two reference points, b the larger: exactly 1 where they are equal, so the difference must not be
+// contracted with the product that one of them came from (see the reference points in the kernel).  A part that saw no key has
+// kNoKey: its weight is 0 beside any other.
+__device__ __forceinline__ float weight(float a, float b) {
+#pragma clang fp contract(off)
+  return __builtin_amdgcn_exp2f(a - b);
+}
 
 // Workgroup (b, split, h), the head running fastest so that workgroups started together read neighbouring addresses.
 // Its keys [split * chunk, min(Nk, (split + 1) * chunk)) are dealt to the wavefronts kUnroll * 64 / G at a time.
-// m and the exponents are in units of log2 (scaled logits times log2 e).
+// Reference points and exponents are in units of log2 (scaled logits times log2 e).
 template <int DT, int D, bool kSplit>
 __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -102,7 +107,11 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) q[i] = elem<DT>(x, i);
   }
-  float o[8], m = -INFINITY, l = 0.f;
+  // m is the maximum of the unscaled logits, mc the reference point of the exponentials: m times the scale, rounded to fp32.
+  // Everything is held relative to the ROUNDED product: its rounding error cancels between P, O and l, and a step that
+  // does not raise the maximum rescales by exactly 1.  (Rescaled against the unrounded product, O and l picked up the
+  // same factor 2^(rounding error) on every step: LSE off by 8e-4 after 256 steps at logits around 1000.)
+  float o[8], m = -INFINITY, mc = kNoKey, l = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] = 0.f;
 
@@ -136,10 +145,11 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
     float m_new = m;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) m_new = fmaxf(m_new, s[u]);
-    // a group that has seen no key yet keeps m = -inf: its exponents are then taken against 0 (all of them are 0)
-    const float mc = (m_new == -INFINITY ? 0.f : m_new) * scale_log2e;
-    const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(m, scale_log2e, -mc));
+    // a group that has seen no key yet keeps m = -inf and kNoKey: the exponentials of its masked keys are 0 against it
+    const float mc_new = m_new == -INFINITY ? kNoKey : m_new * scale_log2e;
+    const float alpha = weight(mc, mc_new);
     m = m_new;
+    mc = mc_new;
     l *= alpha;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] *= alpha;
@@ -157,11 +167,10 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
   }
 
   // merge the lane groups of the wavefront
-  m *= scale_log2e;
-  float m_all = m;
+  float m_all = mc;
 #pragma unroll
   for (int x = G; x < 64; x *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, x));
-  const float w = weight(m, m_all);
+  const float w = weight(mc, m_all);
   l *= w;
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] *= w;
