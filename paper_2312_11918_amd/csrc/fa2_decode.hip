@@ -23,7 +23,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLn2 = 0.69314718055994530942f;
-constexpr float kNoKey = -3.402823466e38f;   // reference point of a part that has seen no key (the lowest finite number)
+constexpr float kNoKey = -3.402823466e38f;   // reference point of a part that has seen no key: the lowest finite number
 constexpr int kMaxWaves = 8;   // wavefronts per workgroup
 constexpr int kUnroll = 4;     // keys per lane group and step (8: 1...7 % slower, 2: 0...5 % slower)
 
@@ -145,8 +145,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
     float m_new = m;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) m_new = fmaxf(m_new, s[u]);
-    // a group that has seen no key yet keeps m = -inf and kNoKey: the exponentials of its masked keys are 0 against it
-    const float mc_new = m_new == -INFINITY ? kNoKey : m_new * scale_log2e;
+    // A group that has seen no key yet keeps m = -inf and kNoKey: the exponentials of its masked keys are 0 against it.  So
+    // are those of logits that overflow once scaled (keys masked by the caller with the lowest value of the type).
+    const float mc_new = fmaxf(m_new * scale_log2e, kNoKey);
     const float alpha = weight(mc, mc_new);
     m = m_new;
     mc = mc_new;
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(D) void fa2_decode_merge_kernel(const float* __rest
   float l = 0.f, sum = 0.f;
 #pragma unroll 8
   for (int s = 0; s < splits; ++s) {
-    const float w = __builtin_amdgcn_exp2f(ml[2 * s] - m);   // every split holds a key: its maximum is finite
+    const float w = __builtin_amdgcn_exp2f(ml[2 * s] - m);   // reference points are finite (kNoKey at least)
     l += w * ml[2 * s + 1];
     sum += w * po[(size_t)s * D];
   }

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(4 * D) void fa2_split_merge_kernel(SplitArgs split,
     const f32x2 x = *reinterpret_cast<const f32x2*>(ml + (size_t)s * 2 * kBr);
     const float* p = po + (size_t)s * kBr * D;
     const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 128);
-    const float w = __builtin_amdgcn_exp2f(x[0] - m);   // every slice holds a visible key of every row: x[0] is finite
+    const float w = __builtin_amdgcn_exp2f(x[0] - m);   // reference points are finite (kLowest at least)
     l += w * x[1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

@@ -51,6 +51,7 @@ constexpr int kBr = 32 * kWaves;     // query rows per workgroup (32 per wavefro
 constexpr int kBc = 64;              // keys per K/V tile
 constexpr int kSpinLimit = 1 << 18;  // polls of the arrival count before a wavefront gives up (tens of milliseconds)
 constexpr int kXcds = 8;             // accelerator complex dies; workgroup i is dispatched to XCD i % 8
+constexpr float kLowest = -3.402823466e38f;   // the lowest finite number
 constexpr float kLazyLog2 = 8.0f;    // the rowmax reference moves only when exceeded by 2^8
 
 // Element-type specifics: the MFMA flavour and the fp32 -> 16-bit pack (round to nearest even).
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
       constexpr bool kSkipIdleRescale = D == 256 || decltype(mask_tag)::value;
       if (!kSkipIdleRescale || __builtin_amdgcn_ballot_w64(move) != 0) {
         const float m_new = move ? mx : m_ref;
-        const float mc_new = m_new * scale_log2e;
+        const float mc_new = kSplit ? fmaxf(m_new * scale_log2e, kLowest) : m_new * scale_log2e;
         // exp(m_old - m_new); 0 on the first tile.  A row that stays (the branch is taken when any row of the
         // wavefront moves) gets exactly 1, not exp2 of a contracted m*c - m*c that may differ from 0 in the last
         // bit: a row's result must not depend on what the other rows of the wavefront hold.
@@ -730,7 +731,10 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
 #pragma unroll
       for (int v = 0; v < 16; ++v) ot[db][v] = 0.f;
     m_ref = -INFINITY;
-    mc_ref = -INFINITY;
+    // kSplit: a part of the keys may hold only logits so low that they overflow once scaled (keys that a caller masks with
+    // the lowest value of the type, past the last tile of the live ones); its reference stops at the lowest finite number,
+    // against which their exponentials are 0.  (A whole launch starts on the first keys, which are live in that use.)
+    mc_ref = kSplit ? kLowest : -INFINITY;
     l_run = 0.f;
 
     // A chained Q tile after the first finds its ring filled, its Q fragment loaded and its first S computed by
@@ -847,7 +851,7 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
         }
       if (hh == 0) ml_lds[half * kRows + wave * 32 + r] = f32x2{mc_ref, l_tot};
       __syncthreads();
-      // half 0 always holds a visible key of every row; half 1 may hold none (reference -inf, sums 0, weight 0)
+      // half 0 always holds a visible key of every row; half 1 may hold none (reference kLowest, sums 0, weight 0)
       const f32x2 ml = ml_lds[(1 - half) * kRows + wave * 32 + r];
       const float m = fmaxf(mc_ref, ml[0]);
       const float w_mine = __builtin_amdgcn_exp2f(mc_ref - m), w_other = __builtin_amdgcn_exp2f(ml[0] - m);

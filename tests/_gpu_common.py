@@ -62,3 +62,17 @@ def rows_one_per_tile(B, H, N, tile, seed, extra=0):
                                                r.integers(0, N, extra)], axis=1)])
     corners = np.array([(0, 0, 0), (B - 1, H - 1, N - 1), (0, H - 1, min(127, N - 1)), (B - 1, 0, min(128, N - 1))])
     return np.concatenate([corners, rows]).astype(np.int32)
+
+
+def mask_by_lowest_value(qb, kb, live, dtype):
+    """Bit patterns of q and k in which the keys from `live` on are masked the way a caller does it with finite numbers: an
+    extra feature that is 1 in every query, 0 in live keys and the lowest value of the type in masked ones (and the scale
+    of the others folded into q, so that the call's own scale is 1)."""
+    torch = torch_gpu()
+    tdt = torch.float16 if dtype == "fp16" else torch.bfloat16
+    q, k = (torch.from_numpy(x.view(np.int16)).view(tdt).clone() for x in (qb, kb))
+    q *= q.shape[-1] ** -0.5
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[:, live:, :, 0] = torch.finfo(tdt).min
+    return tuple(x.view(torch.int16).numpy().view(np.uint16) for x in (q, k))

@@ -7,7 +7,7 @@ import pytest
 import oracle
 import paper_2312_11918_amd as fa2
 from test_gpu_ragged import PAD, SENT16, SENT32, _guarded, _make
-from _gpu_common import torch_gpu
+from _gpu_common import mask_by_lowest_value, torch_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +93,25 @@ def test_single_query_large_logits_over_many_steps(H, Nk, d, dtype, split):
     assert np.all(np.abs(lse - lse_ref) <= 1e-6 * lse_ref)
     half_ulp = 2.0 ** (-11 if dtype == "fp16" else -8)
     assert np.all(np.abs(o - o_ref) <= np.abs(o_ref) * half_ulp + 1e-4 * np.abs(oracle.widen(vb, dtype)).max())
+
+
+@pytest.mark.parametrize("Nk,live,d,dtype", [
+    (600, 30, 128, "bf16"),      # lane groups and wavefronts with masked keys only
+    (4096, 1000, 128, "bf16"),   # splits with masked keys only
+    (9000, 1, 64, "bf16"),
+    (3000, 700, 256, "bf16"),
+    (4096, 1000, 128, "fp16"),   # -65504: no overflow
+])
+@pytest.mark.parametrize("split", [True, False])
+def test_single_query_keys_masked_by_the_lowest_value(Nk, live, d, dtype, split):
+    # the scaled logits of masked keys overflow fp32 in bf16 (lowest value * log2 e); finite inputs, so O and LSE are those of
+    # the live keys
+    print(f"decode masked keys Nk={Nk} live={live} d={d} {dtype} split={split}", flush=True)
+    qb, kb, vb = _make(1, 3, 1, Nk, d, dtype, 7100 + Nk + d, 0.0)
+    qb, kb = mask_by_lowest_value(qb, kb, live, dtype)
+    o_ref, lse_ref = oracle.attention(oracle.widen(qb, dtype), oracle.widen(kb[:, :live].copy(), dtype),
+                                      oracle.widen(vb[:, :live].copy(), dtype), 1.0)
+    o, lse = _decode(qb, kb, vb, dtype, 1.0, split)
+    half_ulp = 2.0 ** (-11 if dtype == "fp16" else -8)
+    assert np.all(np.abs(o - o_ref) <= np.abs(o_ref) * half_ulp + 1e-5)
+    assert np.all(np.abs(lse - lse_ref) <= 1e-5 * np.maximum(1.0, np.abs(lse_ref)))

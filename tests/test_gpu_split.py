@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2312_11918_amd as fa2
 from test_gpu_ragged import _check, _guarded, _make, _run
-from _gpu_common import torch_gpu
+from _gpu_common import mask_by_lowest_value, torch_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +87,38 @@ def test_split_on_another_stream_and_in_a_graph(Nq, Nk, d):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(o, ref) and torch.equal(lse, ref_lse) and bool((junk == 3.0).all())
+
+
+@pytest.mark.parametrize("Nq,Nk,live,d,sliced", [
+    (128, 641, 40, 128, False),    # half 1 sees masked keys only
+    (100, 2000, 64, 64, True),     # ... and slices that do
+    (128, 1024, 1, 128, True),
+    (64, 8192, 5000, 128, True),
+    (200, 4000, 64, 256, True),    # slices without halves
+])
+@pytest.mark.parametrize("workspace", [True, False])
+def test_keys_masked_by_the_lowest_value(Nq, Nk, live, d, sliced, workspace):
+    # scaled logits of masked keys overflow fp32 (lowest bf16 * log2 e); the inputs are finite, so O and LSE are those of the
+    # live keys, also where a half or a slice holds none
+    print(f"split masked keys Nq={Nq} Nk={Nk} live={live} d={d} workspace={workspace}", flush=True)
+    torch = torch_gpu()
+    assert (fa2.fa2_workspace_bytes(1, 2, Nq, Nk, d) > 0) == sliced
+    qb, kb, vb = _make(1, 2, Nq, Nk, d, "bf16", 9100 + Nk + d)
+    qb, kb = mask_by_lowest_value(qb, kb, live, "bf16")
+    o_ref, lse_ref = oracle.attention(oracle.widen(qb, "bf16"), oracle.widen(kb[:, :live].copy(), "bf16"),
+                                      oracle.widen(vb[:, :live].copy(), "bf16"), 1.0)
+    if workspace:
+        o, lse = _run(qb, kb, vb, "bf16", 1.0)
+    else:
+        q, k, v = (_guarded(x, "bf16")[0] for x in (qb, kb, vb))
+        ot = torch.full_like(q, float("nan"))
+        lt = torch.full((1, 2, Nq), float("nan"), dtype=torch.float32, device="cuda")
+        rc = fa2.fa2_fwd_qk_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), ot.data_ptr(), lt.data_ptr(), 1, 2, Nq, Nk, d, 1.0,
+                                fa2.FA2_BF16, fa2.FA2_MASK_NONE, torch.cuda.current_stream().cuda_stream)
+        assert rc == fa2.FA2_OK
+        torch.cuda.synchronize()
+        o, lse = ot.double().cpu().numpy(), lt.double().cpu().numpy()
+    # one ulp of bf16 (P and O are rounded to it) of values up to max |V|
+    assert np.all(np.isfinite(o)) and np.all(np.isfinite(lse))
+    assert np.max(np.abs(o - o_ref)) <= 2.0 ** -7 * np.abs(oracle.widen(vb, "bf16")).max()
+    assert np.max(np.abs(lse - lse_ref)) <= 1e-3
