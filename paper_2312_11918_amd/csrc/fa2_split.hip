@@ -65,7 +65,7 @@ size_t bytes_of(int slices, long long q_tiles, int d) {
   return slices == 1 ? 0 : (size_t)q_tiles * slices * kBr * (d + 2) * sizeof(float);
 }
 
-// The plan for a problem and so many bytes of workspace, by estimated time.
+// The plan for a problem by estimated time, with or without a workspace for slices.
 //
 // The estimates (us) are fits to about thirty shapes, bf16 N(0,1), K and V from HBM, and hold to about 15 %.  A whole
 // launch costs a start plus a time per K/V tile of its longest workgroup.  Halved workgroups pay more to start and
@@ -77,7 +77,7 @@ size_t bytes_of(int slices, long long q_tiles, int d) {
 // mask it runs one workgroup per PAIR of Q tiles, and single ones, longest first, fill the CUs better up to about 1000 Q
 // tiles: B1 H12 N3088 d128 (300) 63.7 / 44.5, B5 H2 N6401 d64 (510) 103.5 / 70.1, B5 H24 N620 d256 (600) 78.6 / 61.3 (d = 256:
 // unpaired, not halved); level from there (B3 H12 N3245 d128, 936 Q tiles: 107.8 / 106.8).
-Plan plan_of(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace) {
+Plan plan_of(int B, int H, int Nq, int Nk, int d, bool causal, bool may_slice) {
   const long long heads = (long long)B * H;
   const int n_q = (Nq + kBr - 1) / kBr, n_k = 2 * ((Nk + kBr - 1) / kBr);
   Plan best{n_k, 1, n_q, false};
@@ -109,8 +109,7 @@ Plan plan_of(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace)
     const long long items = causal ? (long long)slices * n_q - (long long)(chunk / 2) * slices * (slices - 1) / 2
                                    : (long long)slices * n_q;
     const long long groups = heads * items;
-    if (bytes_of(slices, q_tiles, d) > workspace) break;
-    if (slices > 1 && (groups > 2 * kCUs || Nk < FA2_SPLIT_MIN_KEYS)) break;
+    if (slices > 1 && (!may_slice || groups > 2 * kCUs || Nk < FA2_SPLIT_MIN_KEYS)) break;
     const int rounds = (int)((groups + kCUs - 1) / kCUs);
     const int steps = d == 256 ? (chunk < n_k ? chunk : n_k) : chunk / 2;
     const float fill = groups < kCUs ? (float)groups / kCUs : 1.0f;
@@ -131,6 +130,15 @@ Plan plan_of(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace)
   return best;
 }
 
+// The plan that a call with so many bytes of workspace runs: slices only if they fit, otherwise the best plan without any, as
+// for a call with no workspace (a smaller number of slices that fits is not taken: what a call does depends on whether it
+// has the workspace that split_workspace() names, not on how much it has).
+Plan plan_with(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace) {
+  const Plan p = plan_of(B, H, Nq, Nk, d, causal, workspace != 0);
+  if (p.slices == 1 || workspace >= bytes_of(p.slices, (long long)B * H * ((Nq + kBr - 1) / kBr), d)) return p;
+  return plan_of(B, H, Nq, Nk, d, causal, false);
+}
+
 SplitArgs args_of(const Plan& plan, void* workspace, long long q_tiles, int d) {
   SplitArgs a;
   a.part_o = static_cast<float*>(workspace);
@@ -142,7 +150,7 @@ SplitArgs args_of(const Plan& plan, void* workspace, long long q_tiles, int d) {
 }
 
 template <int DT, int D, bool kCausal> int launch(const Problem& p, void* workspace, size_t workspace_bytes) {
-  const Plan plan = plan_of(p.B, p.H, p.Nq, p.Nk, D, kCausal, workspace_bytes);
+  const Plan plan = plan_with(p.B, p.H, p.Nq, p.Nk, D, kCausal, workspace_bytes);
   const int n_q = (p.Nq + kBr - 1) / kBr;
   const SplitArgs split = args_of(plan, workspace, (long long)p.B * p.H * n_q, D);
   const int total = p.B * p.H * plan.items;
@@ -163,11 +171,11 @@ template <int DT, int D> int launch(const Problem& p, void* workspace, size_t wo
 }  // namespace
 
 bool split_accepts(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace) {
-  return plan_of(B, H, Nq, Nk, d, causal, workspace).use;
+  return plan_with(B, H, Nq, Nk, d, causal, workspace).use;
 }
 
 size_t split_workspace(int B, int H, int Nq, int Nk, int d, bool causal) {
-  const Plan p = plan_of(B, H, Nq, Nk, d, causal, SIZE_MAX);
+  const Plan p = plan_of(B, H, Nq, Nk, d, causal, true);
   return p.use ? bytes_of(p.slices, (long long)B * H * ((Nq + kBr - 1) / kBr), d) : 0;
 }
 

@@ -122,3 +122,43 @@ def test_keys_masked_by_the_lowest_value(Nq, Nk, live, d, sliced, workspace):
     assert np.all(np.isfinite(o)) and np.all(np.isfinite(lse))
     assert np.max(np.abs(o - o_ref)) <= 2.0 ** -7 * np.abs(oracle.widen(vb, "bf16")).max()
     assert np.max(np.abs(lse - lse_ref)) <= 1e-3
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d,causal", [
+    (1, 1, 128, 1430, 64, False),    # six slices with the whole workspace; three would fit in a byte less
+    (1, 16, 512, 8192, 128, False),
+    (1, 6, 3000, 3000, 128, True),
+    (1, 4, 300, 3000, 256, False),
+    (1, 8, 1, 4096, 128, False),     # the single-query kernel
+])
+def test_workspace_one_byte_short_and_exact(B, H, Nq, Nk, d, causal):
+    # a byte less than fa2_workspace_bytes(): exactly fa2_fwd_qk, the workspace untouched; exactly that many: not a byte
+    # past the end
+    print(f"workspace edge B={B} H={H} Nq={Nq} Nk={Nk} d={d} causal={causal}", flush=True)
+    torch = torch_gpu()
+    mask = fa2.FA2_MASK_CAUSAL if causal else fa2.FA2_MASK_NONE
+    need = fa2.fa2_workspace_bytes(B, H, Nq, Nk, d, mask)
+    assert need > 0
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q, k, v = (torch.randn((B, n, H, d), generator=g, device="cuda").half() for n in (Nq, Nk, Nk))
+    ws = torch.empty(need + 4096, dtype=torch.uint8, device="cuda")
+
+    def call(ws_ptr, nbytes):
+        ws.fill_(0xA5)
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((B, H, Nq), float("nan"), dtype=torch.float32, device="cuda")
+        args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, Nq, Nk, d, d ** -0.5,
+                fa2.FA2_FP16, mask)
+        stream = torch.cuda.current_stream().cuda_stream
+        rc = fa2.fa2_fwd_qk_raw(*args, stream) if ws_ptr is None else fa2.fa2_fwd_ws_raw(*args, ws_ptr, nbytes, stream)
+        assert rc == fa2.FA2_OK
+        torch.cuda.synchronize()
+        return o, lse
+
+    o_ref, lse_ref = call(None, 0)
+    o, lse = call(ws.data_ptr(), need - 1)
+    assert bool((ws == 0xA5).all()), "a workspace that is too small was written"
+    assert torch.equal(o, o_ref) and torch.equal(lse, lse_ref)
+    o, lse = call(ws.data_ptr(), need)
+    assert bool((ws[need:] == 0xA5).all()) and not bool((ws[:need] == 0xA5).all())
+    assert bool((o.float() - o_ref.float()).abs().max() <= 2e-3) and bool((lse - lse_ref).abs().max() <= 1e-5)
