@@ -57,6 +57,17 @@ int launch(const void* Q, const void* K, const void* V, void* O, float* LSE, int
 
 inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
+// The problems (of positive sizes, with a known mask) that the entry points take.
+bool sizes_fit(int B, int H, int Nq, int Nk, int d, int mask) {
+  if (d != 64 && d != 128 && d != 256) return false;
+  if (mask == FA2_MASK_CAUSAL && Nq != Nk) return false;  // the diagonal is defined for a square S only
+  // element offsets are computed in 64 bits; the row index b*N+n must still fit the tile arithmetic
+  const int n_max = Nq > Nk ? Nq : Nk;
+  if ((long long)B * n_max > 0x7fffffffLL) return false;
+  // the K/V rows of one batch entry are addressed with 32-bit byte offsets from a buffer descriptor
+  return (unsigned long long)n_max * (unsigned long long)H * (unsigned long long)d * 2ull < (1ull << 32);
+}
+
 // The tile shape that FA2_VARIANT_AUTO stands for (sizes already validated by the caller).
 int choose_variant(int B, int H, int Nq, int Nk, int d, int mask) {
   // Measured on MI355X with N(0,1) inputs: when its Q tiles fill whole rounds of the chip's 256 CUs (one workgroup
@@ -89,14 +100,7 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
     return FA2_ERR_INVALID_ARG;
   if (mask != FA2_MASK_NONE && mask != FA2_MASK_CAUSAL) return FA2_ERR_INVALID_ARG;
   if (dtype != FA2_FP16 && dtype != FA2_BF16) return FA2_ERR_UNSUPPORTED;
-  if (d != 64 && d != 128 && d != 256) return FA2_ERR_UNSUPPORTED;
-  if (mask == FA2_MASK_CAUSAL && Nq != Nk) return FA2_ERR_UNSUPPORTED;  // the diagonal is defined for a square S only
-  // element offsets are computed in 64 bits; the row index b*N+n must still fit the tile arithmetic
-  const int n_max = Nq > Nk ? Nq : Nk;
-  if ((long long)B * n_max > 0x7fffffffLL) return FA2_ERR_UNSUPPORTED;
-  // the K/V rows of one batch entry are addressed with 32-bit byte offsets from a buffer descriptor
-  if ((unsigned long long)n_max * (unsigned long long)H * (unsigned long long)d * 2ull >= (1ull << 32))
-    return FA2_ERR_UNSUPPORTED;
+  if (!sizes_fit(B, H, Nq, Nk, d, mask)) return FA2_ERR_UNSUPPORTED;
   if (variant == FA2_VARIANT_AUTO) {
     const fa2::Problem p{Q, K, V, O, LSE, B, H, Nq, Nk, d, scale * 1.44269504088896340736f, dtype, mask == FA2_MASK_CAUSAL,
                          static_cast<hipStream_t>(stream)};
@@ -149,7 +153,8 @@ extern "C" int fa2_fwd_ws(const void* Q, const void* K, const void* V, void* O, 
 }
 
 extern "C" size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int mask) {
-  if (fa2_tile_shape(B, H, Nq, Nk, d, mask) < 0) return 0;
+  if (B <= 0 || H <= 0 || Nq <= 0 || Nk <= 0 || (mask != FA2_MASK_NONE && mask != FA2_MASK_CAUSAL)) return 0;
+  if (!sizes_fit(B, H, Nq, Nk, d, mask)) return 0;
   if (fa2::decode_accepts(B, H, Nq)) return fa2::decode_workspace(B, H, Nk, d);
   return fa2::split_workspace(B, H, Nq, Nk, d, mask == FA2_MASK_CAUSAL);
 }

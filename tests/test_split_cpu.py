@@ -30,3 +30,21 @@ def test_workspace_of_refused_problems_is_zero():
     assert fa2.fa2_workspace_bytes(0, 1, 1, 4096, 64) == 0
     assert fa2.fa2_workspace_bytes(1, 1, 1, 4096, 64, fa2.FA2_MASK_CAUSAL) == 0
     assert fa2.fa2_fwd_ws_raw(4096, 4096, 4096, 4096, None, 1, 1, 1, 4096, 64, 0.125, 0, 0, 4104, 1 << 20) == fa2.FA2_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d", [
+    (1, 1, 1, 1 << 25, 64),              # a batch entry of K of 2^32 bytes
+    (1, 1, 2, 1 << 25, 64),
+    (1, 3, 128, 1 << 24, 128),
+    (1, 1, (1 << 31) - 1, 600, 64),      # 2^31 - 1 queries: the count of Q tiles would overflow
+    (1, 1, 600, (1 << 31) - 1, 64),
+    (512, 1, 1, 1 << 22, 64),            # B * Nk past 2^31 - 1
+])
+def test_workspace_of_problems_past_the_size_limits_is_zero(B, H, Nq, Nk, d):
+    assert fa2.fa2_fwd_ws_raw(4096, 4096, 4096, 4096, None, B, H, Nq, Nk, d, 0.125, 0, 0, None, 0) == fa2.FA2_ERR_UNSUPPORTED
+    assert fa2.fa2_workspace_bytes(B, H, Nq, Nk, d) == 0
+
+
+@pytest.mark.parametrize("mask", [-1, 2])
+def test_workspace_of_an_unknown_mask_is_zero(mask):
+    assert fa2.fa2_workspace_bytes(1, 1, 1, 4096, 64, mask) == 0
