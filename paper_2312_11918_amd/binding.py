@@ -149,6 +149,18 @@ def fa2_fwd_ws_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, Nq, Nk, d, scale, 
                                          stream))
 
 
+def _kept_by_a_graph(torch, tensor) -> bool:
+    """Whether memory allocated during a capture comes from a pool of torch's graphs, which holds it for the graph's replays.
+    In a capture that was begun without torch it comes from the ordinary pool and belongs to other tensors by then."""
+    address = tensor.data_ptr()
+    try:
+        segments = torch.cuda.memory_snapshot()
+    except RuntimeError:   # an allocator that keeps no such record
+        return False
+    return any(s["address"] <= address < s["address"] + s["total_size"] and tuple(s.get("segment_pool_id", (0, 0))) != (0, 0)
+               for s in segments)
+
+
 def _launch(torch, q, k, v, out, lse, scale, dtype, stream, variant, causal) -> int:
     """The call into the library for checked tensors of the current device; returns the C return code.
 
@@ -169,10 +181,13 @@ def _launch(torch, q, k, v, out, lse, scale, dtype, stream, variant, causal) -> 
         nbytes = lib.fa2_workspace_bytes(B, H, N, Nk, d, mask)
         if nbytes:
             # Scratch that belongs to the launch stream: dropped on return, its memory is handed out again only behind
-            # this call's kernels.  Without it the call still runs, its keys unsplit.
+            # this call's kernels, or, in a capture, stays with the graph's pool.  Without it the call still runs, its keys
+            # unsplit.
             try:
                 with nullcontext() if stream is None else torch.cuda.stream(stream):
                     workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
+                    if torch.cuda.is_current_stream_capturing() and not _kept_by_a_graph(torch, workspace):
+                        workspace = None
             except torch.cuda.OutOfMemoryError:
                 pass
     return lib.fa2_fwd_ws(*ptrs, B, H, N, Nk, d, float(scale), dtype, mask,
@@ -188,6 +203,9 @@ def fa2_fwd(q, k, v, scale: float, out=None, lse=None, return_lse: bool = True, 
     false).  The kernel is enqueued on ``stream`` (a ``torch.cuda.Stream``) or on torch's current stream.
     ``variant`` selects the tile shape (``FA2_VARIANT_*``); the default lets the library choose.
     ``causal`` masks S so that query i sees keys j <= i only (``fa2_fwd_masked``; default tile shape only).
+    Where ``fa2_workspace_bytes`` is not 0 the call takes that much scratch from torch's allocator for its own time, with
+    ``out`` and ``lse`` given too (not in a capture begun without torch); ``fa2_fwd_qk_raw`` allocates nothing, and
+    ``fa2_fwd_ws_raw`` uses the caller's scratch.
     """
     import torch
 

@@ -1,5 +1,7 @@
 """GPU parity of the launches that cut the keys (few Q tiles): halves inside a workgroup, slices over workgroups and their
 merge, against the fp64 CPU oracle on guarded buffers, with the tolerances of the whole launches."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -162,3 +164,46 @@ def test_workspace_one_byte_short_and_exact(B, H, Nq, Nk, d, causal):
     o, lse = call(ws.data_ptr(), need)
     assert bool((ws[need:] == 0xA5).all()) and not bool((ws[:need] == 0xA5).all())
     assert bool((o.float() - o_ref.float()).abs().max() <= 2e-3) and bool((lse - lse_ref).abs().max() <= 1e-5)
+
+
+@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128)])
+def test_capture_begun_without_torch_holds_no_pool_memory(Nq, Nk, d):
+    # nothing keeps torch's ordinary memory for such a graph: the call must leave its keys unsplit rather than take scratch
+    # that other tensors own when the graph is replayed
+    print(f"raw capture Nq={Nq} Nk={Nk}", flush=True)
+    torch = torch_gpu()
+    H = 8
+    need = fa2.fa2_workspace_bytes(1, H, Nq, Nk, d)
+    assert need > 0
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn((1, n, H, d), generator=g, device="cuda").half() for n in (Nq, Nk, Nk))
+    ref = torch.empty_like(q)
+    ref_lse = torch.empty((1, H, Nq), dtype=torch.float32, device="cuda")
+    assert fa2.fa2_fwd_qk_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), ref.data_ptr(), ref_lse.data_ptr(), 1, H, Nq, Nk, d,
+                              d ** -0.5, fa2.FA2_FP16, fa2.FA2_MASK_NONE,
+                              torch.cuda.current_stream().cuda_stream) == fa2.FA2_OK
+    o, lse = torch.empty_like(ref), torch.empty_like(ref_lse)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    fa2.fa2_fwd(q, k, v, d ** -0.5, out=o, lse=lse, stream=side)   # the side stream's pool now holds a block of that size
+    torch.cuda.synchronize()
+    hip = fa2.load_library()   # its dependency, the HIP runtime, resolves through it
+    stream, graph, graph_exec = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    thread_local_mode = 1
+    assert hip.hipStreamBeginCapture(stream, thread_local_mode) == 0
+    try:
+        fa2.fa2_fwd(q, k, v, d ** -0.5, out=o, lse=lse, stream=side)
+    finally:
+        assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    assert hip.hipGraphInstantiate(ctypes.byref(graph_exec), graph, None, None, ctypes.c_size_t(0)) == 0
+    with torch.cuda.stream(side):
+        junk = [torch.full((need,), 7, dtype=torch.uint8, device="cuda") for _ in range(3)]
+    for _ in range(3):
+        o.fill_(float("nan"))
+        lse.fill_(float("nan"))
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(graph_exec, stream) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
+        assert all(bool((x == 7).all()) for x in junk)
+    assert hip.hipGraphExecDestroy(graph_exec) == 0 and hip.hipGraphDestroy(graph) == 0
