@@ -76,7 +76,10 @@ int fa2_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, in
 enum {
   FA2_VARIANT_AUTO = 0,   /* pick by problem shape (what fa2_fwd does)                                  */
   FA2_VARIANT_NARROW = 1, /* 128 query rows per workgroup (4 wavefronts x 32 rows), 2 workgroups per CU,
-                             K/V tiles of 64 keys double-buffered in LDS                                */
+                             K/V tiles of 64 keys double-buffered in LDS.  The form that FA2_VARIANT_AUTO runs
+                             with the keys of few Q tiles cut into halves (8 wavefronts) waits on counters in LDS;
+                             the waits are bounded (about ten milliseconds): should a wavefront ever give up, all
+                             rows of its workgroup come out as NaN instead of the launch hanging              */
   FA2_VARIANT_NARROW8 = 3 /* 256 query rows per workgroup (8 wavefronts x 32 rows), 1 workgroup per CU,
                              K/V loaded three tiles ahead, half the L2 -> LDS traffic per FLOP, no barrier
                              in the loop (the wavefronts count arrivals in LDS with one tile of slack);

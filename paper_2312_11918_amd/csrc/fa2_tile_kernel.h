@@ -229,7 +229,9 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
   __shared__ __attribute__((aligned(1024))) uint16_t v_lds2[kNBuf == 4 ? T::kElems : 8];
   __shared__ __attribute__((aligned(1024))) uint16_t v_lds3[kNBuf == 4 ? T::kElems : 8];
   __shared__ f32x2 ml_lds[kHalves ? 2 * kRows : 1];  // reference point and row sum of either half, for the other
-  __shared__ uint32_t arrivals[4];  // kFlagSync: wavefronts that finished iteration j, counted in entry j % 4
+  // kFlagSync: wavefronts that finished iteration j, counted in entry j % 4.  kHalves: arrivals of either half at its barrier
+  // (entries 0 and 1), and whether a wavefront has given up waiting (entry 2)
+  __shared__ uint32_t arrivals[4];
   // kRowStores: 32 rows x 32 columns of O per wavefront, through which the result is turned from one query per
   // lane into whole 64-byte pieces of rows before it is stored: a lane-per-query store touches 64 rows per
   // instruction, and the epilogue of a Q tile then costs thousands of cycles that only partly hide behind the other
@@ -662,13 +664,15 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     if constexpr (kHalves) {
       // A barrier of this half's four wavefronts, counted in LDS: s_barrier would stop all eight at every tile and keep
       // the two wavefronts of a SIMD, one of either half, in the same phase, softmax against softmax and MFMAs against
-      // MFMAs.  The wait is bounded like the one above.
+      // MFMAs.  The wait is bounded like the one above (without a sleep between polls: about ten milliseconds).  A
+      // wavefront that gives up refills buffers that slower ones of its half may still read, so it poisons the row sums
+      // of the whole workgroup, not only its own.
       if (lane == 0) __hip_atomic_fetch_add(&arrivals[half], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       int spins = 0;
       while (__hip_atomic_load(&arrivals[half], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
              (uint32_t)(kRowWaves * (j + 1))) {
         if (++spins > kSpinLimit) {
-          l_run = __builtin_nanf("");
+          __hip_atomic_store(&arrivals[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // read in the epilogue
           break;
         }
       }
@@ -857,6 +861,7 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
       const float w_mine = __builtin_amdgcn_exp2f(mc_ref - m), w_other = __builtin_amdgcn_exp2f(ml[0] - m);
       mc_ref = m;
       l_tot = l_tot * w_mine + ml[1] * w_other;
+      if (__hip_atomic_load(&arrivals[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) l_tot = __builtin_nanf("");
 #pragma unroll
       for (int db = 0; db < kMyBlocks; ++db)
 #pragma unroll
