@@ -178,8 +178,8 @@ struct SplitArgs {
 };
 
 // Wavefronts per SIMD: at d = 64 the 4-wavefront kernels are held to 168 registers, three workgroups per CU.  With the
-// causal mask and partial tiles they took 195 before, two workgroups per CU: B50 H16 N330 fp16 56 -> 49 us, B60 H24 N140 fp16
-// 36.0 -> 31.6, B30 H8 N700 bf16 36.1 -> 32.8; whole tiles B40 H16 N384 bf16 42.0 -> 41.4, B8 H32 N2048 fp16 180 -> 178.
+// causal mask and partial tiles they took 195 before, two workgroups per CU: B50 H16 N330 fp16 54.7 -> 46.8 us, B60 H24 N140
+// fp16 36.2 -> 31.5, B30 H8 N700 bf16 34.7 -> 30.2; level where two workgroups per CU hold the whole grid (see kOneOffset).
 template <int DT, int D, int kWv, int kNBuf, bool kCausal, bool kRagged, bool kSplit = false>
 __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <= 128 ? 2 : 1) void fa2_fwd_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -341,11 +341,14 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
       lds_tile += half_lds;
     }
     // d = 256 with partial tiles has no registers to spare for sixteen loop-invariant source offsets: keep them
-    // from being hoisted out of the loop (they cost a few integer operations per load to recompute).  Nor has d = 64
-    // with the causal mask and partial tiles at three wavefronts per SIMD.  (At d = 128 the registers that this frees,
-    // 256 -> 230, would do for kRowStores, but the loop lost 6 % at N = 5000.)
-    if constexpr ((D == 256 || (D == 64 && kCausal)) && kRagged) asm volatile("" : "+v"(lane));
+    // from being hoisted out of the loop (they cost a few integer operations per load to recompute).  (At d = 128 the
+    // registers that this frees, 256 -> 230, would do for kRowStores, but the loop lost 6 % at N = 5000.)
+    if constexpr (D == 256 && kRagged) asm volatile("" : "+v"(lane));
+    // d = 64 with the causal mask and partial tiles has few to spare at three wavefronts per SIMD: here one offset per
+    // operand is kept, and nothing for the last tiles.
+    constexpr bool kOneOffset = D == 64 && kCausal && kRagged;
     if (kRagged && (j + 1) * kBc > Nk) {
+      if constexpr (kOneOffset) asm volatile("" : "+v"(lane));
       // a tile with rows past the last key: those rows are filled with copies of the last key's row, so LDS
       // holds finite numbers everywhere (their columns of S are masked; 0 * finite = 0 in GEMM-II)
 #pragma unroll
@@ -358,6 +361,23 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(lds_tile + 512 * (wave * kLoadsPerWave + i)), 16,
                                                  (int)src, 0, 0, 0);
       }
+      return;
+    }
+    if constexpr (kOneOffset) {
+      // The second load is eight rows further on, a scalar distance: V's swizzle repeats there, K's differs in bit 2 of the
+      // 16-byte chunk (a row of a head is 128 bytes, so that is bit 6 of the offset).  With all four offsets recomputed at
+      // every tile instead, calls of up to two workgroups per CU lost 2...6 % (B7 H16 N412 fp16 14.4 -> 15.3 us, now 14.5;
+      // B10 H16 N650 22.2 -> 23.2, now 22.1) and long ones as much (B4 H16 N5001 fp16 251 us, now 232).
+      static_assert(!kOneOffset || kLoadsPerWave == 2, "two loads per tile and wavefront");
+      const int chunk = 64 * wave * kLoadsPerWave + lane;
+      const int row = chunk / T::kChunksPerRow, pos = chunk % T::kChunksPerRow;
+      const int swz = decltype(is_k)::value ? T::swz_k(row) : T::swz_v(row);
+      const uint32_t src = (uint32_t)row * row_bytes + 16u * (uint32_t)(pos ^ swz);
+      uint16_t* const dst = lds_tile + 512 * wave * kLoadsPerWave;
+      const uint32_t at = (uint32_t)j * tile_bytes;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)dst, 16, (int)src, (int)at, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + 512), 16,
+                                               (int)(decltype(is_k)::value ? src ^ 64u : src), (int)(at + 8u * row_bytes), 0, 0);
       return;
     }
 #pragma unroll
