@@ -8,10 +8,9 @@
 #include <tuple>
 
 #include "fa2.h"
+#include "fa2_split_plan.h"
 
 namespace fa2 {
-
-constexpr int kCUs = 256;  // compute units of the whole chip (choice of tile shapes and of key splits)
 
 // A problem that has passed validation.
 struct Problem {
