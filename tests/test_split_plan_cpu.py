@@ -41,3 +41,25 @@ def test_d256_without_a_mask_is_never_the_whole_launch_in_another_kernel(plan):
                 for Nq in (128, 200, 512, 1000, 1024, 2048, 4096) for Nk in (300, 512, 1024, 2000, 4096, 8192) for may in (0, 1)]
     for p, (use, _, slices, _) in zip(problems, plan(problems)):
         assert not use or slices > 1, p
+
+
+# B, H, N, d: causal problems, us whole / with single Q tiles in one slice (no workspace)
+WHOLE = [
+    (1, 16, 4096, 256), (1, 8, 4096, 256), (2, 8, 2048, 256),   # 144 / 160, 122 / 136, 69.6 / 72.2: whole tiles, chained
+    (2, 12, 2560, 256), (3, 6, 3328, 256), (8, 2, 3840, 256),   # 96 / 104, 120 / 132, 135 / 145
+    (10, 2, 3071, 256), (1, 16, 4059, 256), (99, 1, 462, 256),  # partial tiles: 117 / 122, 158 / 163, 36.1 / 38.4
+    (8, 12, 512, 128), (7, 16, 384, 128), (5, 16, 640, 128),    # 19.3 / 20.9, 17.2 / 18.4, 21.4 / 22.1
+    (8, 12, 512, 64), (7, 16, 384, 64),                         # 13.9 / 14.8, 12.6 / 13.2
+]
+SINGLE = [
+    (1, 12, 3072, 128), (1, 24, 1536, 128), (8, 1, 4395, 128),  # 56.8 / 42.8, 33.8 / 25.4, 78.0 / 57.2
+    (1, 32, 1127, 64), (2, 12, 1920, 64), (8, 2, 4736, 64),     # 21.0 / 15.4, 27.7 / 21.9, 80.8 / 66.9
+    (16, 2, 2272, 256), (1, 24, 2632, 256), (3, 12, 1920, 256), # 176 / 123, 152 / 115, 139 / 100
+    (8, 8, 512, 256), (2, 24, 731, 256),                        # 31.0 / 25.4, 40.4 / 33.5
+]
+
+
+def test_causal_problems_without_a_workspace(plan):
+    problems = [(B, H, N, N, d, 1, 0) for B, H, N, d in WHOLE + SINGLE]
+    for i, (p, (use, _, slices, _)) in enumerate(zip(problems, plan(problems))):
+        assert slices == 1 and bool(use) == (i >= len(WHOLE)), p
