@@ -345,10 +345,10 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     // registers that this frees, 256 -> 230, would do for kRowStores, but the loop lost 6 % at N = 5000.)
     if constexpr (D == 256 && kRagged) asm volatile("" : "+v"(lane));
     // d = 64 with the causal mask and partial tiles has few to spare at three wavefronts per SIMD: here one offset per
-    // operand is kept, and nothing for the last tiles.
+    // operand is kept, and nothing for the last tiles (whose offsets the halves, with two per SIMD, may keep: 2 % at N = 638).
     constexpr bool kOneOffset = D == 64 && kCausal && kRagged;
     if (kRagged && (j + 1) * kBc > Nk) {
-      if constexpr (kOneOffset) asm volatile("" : "+v"(lane));
+      if constexpr (kOneOffset && !kSplit) asm volatile("" : "+v"(lane));
       // a tile with rows past the last key: those rows are filled with copies of the last key's row, so LDS
       // holds finite numbers everywhere (their columns of S are masked; 0 * finite = 0 in GEMM-II)
 #pragma unroll
