@@ -105,10 +105,10 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
     const fa2::Problem p{Q, K, V, O, LSE, B, H, Nq, Nk, d, scale * 1.44269504088896340736f, dtype, mask == FA2_MASK_CAUSAL,
                          static_cast<hipStream_t>(stream)};
     if (fa2::decode_accepts(B, H, Nq)) return fa2::decode(p, workspace, workspace_bytes);
-    if (workspace == nullptr) workspace_bytes = 0;
-    if (fa2::split_accepts(B, H, Nq, Nk, d, p.causal, workspace_bytes)) return fa2::split_tiles(p, workspace, workspace_bytes);
+    int rc;
+    if (fa2::split_tiles(p, workspace, workspace_bytes, &rc)) return rc;
+    variant = choose_variant(B, H, Nq, Nk, d, mask);
   }
-  if (variant == FA2_VARIANT_AUTO) variant = choose_variant(B, H, Nq, Nk, d, mask);
   if (variant != FA2_VARIANT_NARROW) {
     // the 256-row shape: whole tiles, square, d <= 128
     if (Nq != Nk || Nq % kRows256 != 0 || d == 256) return FA2_ERR_UNSUPPORTED;

@@ -41,10 +41,10 @@ __attribute__((visibility("hidden"))) size_t decode_workspace(int B, int H, int 
 __attribute__((visibility("hidden"))) int decode(const Problem& p, void* workspace, size_t workspace_bytes);
 
 // fa2_split.hip: several queries, but too few Q tiles to fill the chip.  split_workspace() is 0 when the keys are not cut
-// into slices; with fewer bytes than it says they are not either, only into halves.
-__attribute__((visibility("hidden"))) bool split_accepts(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace);
+// into slices; with fewer bytes than it says they are not either, only into halves.  split_tiles() launches nothing and is
+// false where the whole launch is the better one; otherwise *rc is the launch's return code.
 __attribute__((visibility("hidden"))) size_t split_workspace(int B, int H, int Nq, int Nk, int d, bool causal);
-__attribute__((visibility("hidden"))) int split_tiles(const Problem& p, void* workspace, size_t workspace_bytes);
+__attribute__((visibility("hidden"))) bool split_tiles(const Problem& p, void* workspace, size_t workspace_bytes, int* rc);
 
 }  // namespace fa2
 #endif  // FA2_INTERNAL_H_

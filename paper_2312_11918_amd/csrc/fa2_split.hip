@@ -81,8 +81,7 @@ SplitArgs args_of(const SplitPlan& plan, void* workspace, long long q_tiles, int
   return a;
 }
 
-template <int DT, int D, bool kCausal> int launch(const Problem& p, void* workspace, size_t workspace_bytes) {
-  const SplitPlan plan = plan_with(p.B, p.H, p.Nq, p.Nk, D, kCausal, workspace_bytes);
+template <int DT, int D, bool kCausal> int launch(const Problem& p, const SplitPlan& plan, void* workspace) {
   const int n_q = (p.Nq + kBr - 1) / kBr;
   const SplitArgs split = args_of(plan, workspace, (long long)p.B * p.H * n_q, D);
   const int total = p.B * p.H * plan.items;
@@ -96,30 +95,30 @@ template <int DT, int D, bool kCausal> int launch(const Problem& p, void* worksp
                  p.Nq, n_q);
 }
 
-template <int DT, int D> int launch(const Problem& p, void* workspace, size_t workspace_bytes) {
-  return p.causal ? launch<DT, D, true>(p, workspace, workspace_bytes) : launch<DT, D, false>(p, workspace, workspace_bytes);
+template <int DT, int D> int launch(const Problem& p, const SplitPlan& plan, void* workspace) {
+  return p.causal ? launch<DT, D, true>(p, plan, workspace) : launch<DT, D, false>(p, plan, workspace);
 }
 
 }  // namespace
-
-bool split_accepts(int B, int H, int Nq, int Nk, int d, bool causal, size_t workspace) {
-  return plan_with(B, H, Nq, Nk, d, causal, workspace).use;
-}
 
 size_t split_workspace(int B, int H, int Nq, int Nk, int d, bool causal) {
   const SplitPlan p = split_plan(B, H, Nq, Nk, d, causal, true);
   return p.use ? bytes_of(p.slices, (long long)B * H * ((Nq + kBr - 1) / kBr), d) : 0;
 }
 
-int split_tiles(const Problem& p, void* workspace, size_t workspace_bytes) {
+bool split_tiles(const Problem& p, void* workspace, size_t workspace_bytes, int* rc) {
+  const SplitPlan plan = plan_with(p.B, p.H, p.Nq, p.Nk, p.d, p.causal, workspace == nullptr ? 0 : workspace_bytes);
+  if (!plan.use) return false;
   if (p.dtype == FA2_FP16) {
-    return p.d == 64    ? launch<FA2_FP16, 64>(p, workspace, workspace_bytes)
-           : p.d == 128 ? launch<FA2_FP16, 128>(p, workspace, workspace_bytes)
-                        : launch<FA2_FP16, 256>(p, workspace, workspace_bytes);
+    *rc = p.d == 64    ? launch<FA2_FP16, 64>(p, plan, workspace)
+          : p.d == 128 ? launch<FA2_FP16, 128>(p, plan, workspace)
+                       : launch<FA2_FP16, 256>(p, plan, workspace);
+  } else {
+    *rc = p.d == 64    ? launch<FA2_BF16, 64>(p, plan, workspace)
+          : p.d == 128 ? launch<FA2_BF16, 128>(p, plan, workspace)
+                       : launch<FA2_BF16, 256>(p, plan, workspace);
   }
-  return p.d == 64    ? launch<FA2_BF16, 64>(p, workspace, workspace_bytes)
-         : p.d == 128 ? launch<FA2_BF16, 128>(p, workspace, workspace_bytes)
-                      : launch<FA2_BF16, 256>(p, workspace, workspace_bytes);
+  return true;
 }
 
 }  // namespace fa2
