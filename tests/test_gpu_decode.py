@@ -42,7 +42,10 @@ def _decode(qb, kb, vb, dtype, scale, split):
     (1, 2, 17, 128, "fp16", 0.0),
     (3, 1, 31, 64, "bf16", 0.0),         # steps of 32
     (3, 2, 33, 64, "fp16", 0.02),
-    (2, 5, 257, 128, "fp16", 0.0),       # one key past what sixteen wavefronts take in a step
+    (2, 5, 128, 128, "bf16", 0.0),       # a full step of eight wavefronts
+    (2, 5, 129, 128, "fp16", 0.0),       # one key past it
+    (2, 5, 257, 128, "fp16", 0.0),       # one key past two
+    (3, 2, 130, 64, "bf16", 0.0),        # eight wavefronts of which three hold no key
     (33, 8, 300, 64, "bf16", 0.0),       # more heads than CUs
     (70, 8, 513, 128, "fp16", 0.0),      # ... and than twice the CUs
     (1, 2, 2047, 64, "fp16", 0.0),       # the last length that is not split at d = 64

@@ -35,3 +35,11 @@ def test_register_and_lds_budgets_match_the_launch_shapes(kernels):
             assert total <= 256 and k["waves_per_simd"] >= 2, k
             per_cu = k["lds_bytes_per_workgroup"] * (2 if "4 wavefronts" in k["name"] else 1)
             assert per_cu <= 160 * 1024, k
+
+
+def test_three_wavefronts_per_simd_at_d64(kernels):
+    # the 128-row shape at d = 64 runs three workgroups of four wavefronts per CU, in every mask and partial-tile form
+    mine = [k for k in kernels if "d=64, 4 wavefronts" in k["name"]]
+    assert len(mine) == 2 * 4
+    for k in mine:
+        assert k["waves_per_simd"] >= 3 and 3 * k["lds_bytes_per_workgroup"] <= 160 * 1024, k

@@ -48,3 +48,28 @@ def test_workspace_of_problems_past_the_size_limits_is_zero(B, H, Nq, Nk, d):
 @pytest.mark.parametrize("mask", [-1, 2])
 def test_workspace_of_an_unknown_mask_is_zero(mask):
     assert fa2.fa2_workspace_bytes(1, 1, 1, 4096, 64, mask) == 0
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    return build.resource_usage(build.SPLIT_SOURCES)
+
+
+def test_every_split_kernel_is_reported(kernels):
+    # 2 element types x 3 head dimensions x (the single-query kernel with and without split keys, its merge, the tile kernel
+    #                                        with the keys cut and its merge, with and without the causal mask)
+    names = {k["name"] for k in kernels}
+    assert len(kernels) == len(names) == 2 * 3 * (2 + 1 + 2 + 2), sorted(names)
+
+
+def test_split_kernels_fit_their_launches(kernels):
+    for k in kernels:
+        lds = k["lds_bytes_per_workgroup"]
+        if "8 wavefronts" in k["name"]:      # halves: two wavefronts per SIMD, one workgroup per CU
+            assert k["vgprs"] + k["agprs"] <= 256 and k["waves_per_simd"] >= 2 and lds <= 160 * 1024, k
+        elif "fwd_kernel" in k["name"]:      # d = 256: one wavefront per SIMD
+            assert k["vgprs"] + k["agprs"] <= 512 and lds <= 160 * 1024, k
+        elif "decode_kernel" in k["name"]:   # latency is hidden by wavefronts: two workgroups of eight per CU
+            assert k["waves_per_simd"] >= 4 and 2 * lds <= 160 * 1024, k
+        else:
+            assert k["waves_per_simd"] >= 7 and lds == 0, k
