@@ -11,7 +11,9 @@
 //
 //  * every lane group keeps its own running maximum, row sum and piece of O over the keys it sees; they are merged
 //    once at the end, within the wavefront by lane exchanges, between wavefronts through LDS;
-//  * K of the next step is loaded while this step's softmax runs, V of the next while K of the next is consumed;
+//  * K of the next step is requested as soon as this step's dot products have consumed K, V of the next once this step's
+//    sums have consumed V; a step of the loop ends with both landed (the compiler waits for all loads before it moves them
+//    into the registers of the next step), so what hides their latency is the CU's other wavefronts;
 //  * the keys of a head are split over `splits` workgroups when B*H workgroups do not fill the CUs.  Partial
 //    (O, maximum, sum) then go to the caller's workspace in fp32 and a second kernel merges them.
 #include "fa2_internal.h"
@@ -125,7 +127,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
     for (int u = 0; u < kUnroll; ++u) vx[u] = row(vp, key0 + u * kKeys);
   }
   for (; key0 - group <= last; key0 += stride) {
-    const bool more = key0 - group + stride <= last;   // wavefront-uniform
+    const bool more = key0 - group + stride <= last;   // the same in all lanes (but held per lane)
     float s[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
@@ -264,7 +266,8 @@ Plan plan_of(int B, int H, int Nk, int d, bool may_split) {
       p.splits = (Nk + p.chunk - 1) / p.chunk;
     }
   }
-  while (p.waves > 1 && (p.waves / 2) * step >= p.chunk) p.waves /= 2;   // no wavefront without a key
+  // At least half of the wavefronts hold a key; the others (130 keys at d = 64: three of eight) merge with weight 0.
+  while (p.waves > 1 && (p.waves / 2) * step >= p.chunk) p.waves /= 2;
   // Unsplit heads that fill the CUs read faster as fewer streams: 41.1 against 44.4 us at B16 H16 Nk2048 d128, 33.3
   // against 35.0 at 320 heads of 1000 keys; level (39.9 / 38.7) at 576 heads.  From 2048 heads on four wavefronts
   // also keep the launch's thread count within 32 bits for every problem the tile kernels take.

@@ -177,4 +177,4 @@ extern "C" const char* fa2_strerror(int code) {
   }
 }
 
-extern "C" int fa2_version(void) { return 500; /* 0.5.0 */ }
+extern "C" int fa2_version(void) { return 600; /* 0.6.0 */ }
