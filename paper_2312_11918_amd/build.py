@@ -10,6 +10,7 @@ _ROOT = os.path.dirname(_PKG)
 SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile kernels and the C ABI
 SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query per sequence, keys split
                  os.path.join(_PKG, "csrc", "fa2_split.hip")]        # few query tiles, keys split
+STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64, 64 query rows per wavefront
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
 PROBE_SOURCES = [os.path.join(_PKG, "csrc", "mfma_probe.hip")]
@@ -37,7 +38,7 @@ def _hipcc(sources, library, verbose):
 def build_library(verbose: bool = False) -> str:
     """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
-    return _hipcc([*SOURCES, *SPLIT_SOURCES], LIBRARY, verbose)
+    return _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES], LIBRARY, verbose)
 
 
 def resource_usage(sources=SOURCES):
@@ -78,6 +79,11 @@ def resource_usage(sources=SOURCES):
             k["name"] = (f"fa2_fwd_kernel<{'fp16' if dt == 0 else 'bf16'}, d={d}, {wv} wavefronts, {nbuf} LDS buffers"
                          f"{', causal' if causal else ''}{', partial tiles' if ragged else ''}{', keys cut' if cut else ''}>")
             continue
+        m = re.search(r"fa2_stage_kernelILi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
+        if m:
+            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d=64{', causal' if m[2] == '1' else ''}"
+                         f"{', partial tiles' if m[3] == '1' else ''}>")
+            continue
         m = re.search(r"(fa2_(?:decode|decode_merge|split_merge)_kernel)ILi(\d+)ELi(\d+)E(?:Lb(\d)E)?", k["mangled"])
         if m:
             flag = {None: "", "0": ""}.get(m[4], ", causal" if "split" in m[1] else ", keys split")
@@ -91,7 +97,7 @@ if __name__ == "__main__":
     import sys
 
     if "--resource-usage" in sys.argv:
-        rows = resource_usage([*SOURCES, *SPLIT_SOURCES])
+        rows = resource_usage([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES])
         print("| kernel | VGPRs | AGPRs | SGPRs | scratch B/lane | LDS B/workgroup | wavefronts/SIMD |")
         print("|---|---|---|---|---|---|---|")
         for k in sorted(rows, key=lambda r: r["name"]):

@@ -106,7 +106,7 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
                          static_cast<hipStream_t>(stream)};
     if (fa2::decode_accepts(B, H, Nq)) return fa2::decode(p, workspace, workspace_bytes);
     int rc;
-    if (fa2::split_tiles(p, workspace, workspace_bytes, &rc)) return rc;
+    if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc)) return rc;
     variant = choose_variant(B, H, Nq, Nk, d, mask);
   }
   if (variant != FA2_VARIANT_NARROW) {

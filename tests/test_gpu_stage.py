@@ -1,0 +1,76 @@
+"""GPU parity of the kernel with 64 query rows per wavefront (d = 64, many Q tiles) against the fp64 CPU oracle on guarded buffers,
+with the tolerances of the other launches, at the edges of its stages (32 keys), tiles (64 keys) and workgroups (256 rows)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2312_11918_amd as fa2
+from test_gpu_ragged import _check, _make, _run
+from _gpu_common import mask_by_lowest_value
+
+pytestmark = pytest.mark.gpu
+
+# B, H, Nq, Nk, dtype, causal, outliers: all of them problems that stage_accepts() takes (test_stage_plan_cpu.py).  Outlier keys
+# make P nearly one-hot and outputs as large as V: in bf16 half an ulp of an output in [4, 8) is 1.6e-2, beyond the tolerance of
+# 1e-2 before any arithmetic (2.1e-2 seen at 65 keys with outliers), so they go with fp16 (half an ulp there 2e-3).
+CASES = [
+    (26, 16, 256, 1, "fp16", False, 0.0),        # one key: one stage with one column
+    (26, 16, 255, 32, "bf16", False, 0.0),       # one stage, the other half of the tile masked
+    (26, 16, 193, 33, "fp16", False, 0.0),       # two stages; a last wavefront of one row
+    (26, 16, 192, 64, "fp16", False, 0.0),       # a wavefront without a row
+    (26, 16, 250, 65, "fp16", False, 0.02),      # a second tile of one key
+    (32, 16, 256, 128, "fp16", False, 0.0),      # whole tiles, no boundary with a refill
+    (13, 16, 512, 192, "bf16", False, 0.0),
+    (26, 16, 256, 448, "fp16", False, 0.05),     # odd count of tiles; the reference point moves
+    (8, 25, 511, 257, "fp16", False, 0.0),
+    (8, 8, 2048, 2048, "bf16", True, 0.0),       # whole tiles; heads in groups
+    (7, 9, 2049, 2049, "fp16", True, 0.01),      # heads not a multiple of 8; a last Q tile of one row
+    (8, 9, 1985, 1985, "fp16", True, 0.0),
+]
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,dtype,causal,outliers", CASES)
+def test_stage_parity(B, H, Nq, Nk, dtype, causal, outliers):
+    print(f"stage case B={B} H={H} Nq={Nq} Nk={Nk} {dtype} causal={causal}", flush=True)
+    qb, kb, vb = _make(B, H, Nq, Nk, 64, dtype, 47000 + Nq + Nk, outliers)
+    scale = 0.125
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale, causal=causal)
+    o, lse = _run(qb, kb, vb, dtype, scale, causal)
+    _check(o, lse, o_ref, lse_ref, "stage")
+
+
+@pytest.mark.parametrize("live", [1, 33, 64, 100])
+def test_keys_masked_by_the_lowest_value(live):
+    # scaled logits of masked keys overflow fp32; O and LSE are those of the live keys, also over stages that hold none
+    print(f"stage masked keys live={live}", flush=True)
+    B, H, Nq, Nk = 26, 16, 256, 200
+    qb, kb, vb = _make(B, H, Nq, Nk, 64, "bf16", 9300 + live)
+    qb, kb = mask_by_lowest_value(qb, kb, live, "bf16")
+    o_ref, lse_ref = oracle.attention(oracle.widen(qb, "bf16"), oracle.widen(kb[:, :live].copy(), "bf16"),
+                                      oracle.widen(vb[:, :live].copy(), "bf16"), 1.0)
+    o, lse = _run(qb, kb, vb, "bf16", 1.0)
+    _check(o, lse, o_ref, lse_ref, "masked keys")
+
+
+def test_first_keys_masked_by_the_lowest_value():
+    # the first stage holds no live key: its reference stops at the lowest finite number and moves with the second
+    B, H, Nq, Nk, dead = 26, 16, 256, 128, 40
+    print("stage first keys masked", flush=True)
+    qb, kb, vb = _make(B, H, Nq, Nk, 64, "bf16", 9400)
+    qb, kb = mask_by_lowest_value(qb, kb[:, ::-1].copy(), Nk - dead, "bf16")
+    kb, live = kb[:, ::-1].copy(), slice(dead, None)   # masked keys first
+    o_ref, lse_ref = oracle.attention(oracle.widen(qb, "bf16"), oracle.widen(kb[:, live].copy(), "bf16"),
+                                      oracle.widen(vb[:, live].copy(), "bf16"), 1.0)
+    o, lse = _run(qb, kb, vb, "bf16", 1.0)
+    _check(o, lse, o_ref, lse_ref, "first keys masked")
+
+
+def test_a_rows_bits_do_not_depend_on_its_neighbours():
+    # which rows move their reference is decided from their own values: outlier keys, and the same rows in other company
+    print("stage bits", flush=True)
+    B, H, N = 26, 16, 256
+    qb, kb, vb = _make(B, H, N, N, 64, "fp16", 47777, 0.05)
+    o, lse = _run(qb, kb, vb, "fp16", 0.125)
+    order = np.random.Generator(np.random.PCG64(3)).permutation(N)
+    o2, lse2 = _run(qb[:, order].copy(), kb, vb, "fp16", 0.125)
+    assert np.array_equal(o[:, order], o2) and np.array_equal(lse[:, :, order], lse2)

@@ -1,0 +1,58 @@
+"""Which problems run with 64 query rows per wavefront, and the compiled form of that kernel, on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2312_11918_amd import build
+from test_gpu_stage import CASES
+
+PROGRAM = r"""
+#include <stdio.h>
+#include "fa2_stage_plan.h"
+int main() {
+  int B, H, Nq, Nk, d, causal;
+  while (scanf("%d %d %d %d %d %d", &B, &H, &Nq, &Nk, &d, &causal) == 6)
+    printf("%d\n", fa2::stage_accepts(B, H, Nq, d, causal != 0) && !fa2::split_plan(B, H, Nq, Nk, d, causal != 0, true).use);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def taken(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("plan")
+    source, program = folder / "plan.cc", folder / "plan"
+    source.write_text(PROGRAM)
+    csrc = os.path.dirname(build.SOURCES[0])
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(source), "-o", str(program)], check=True)
+
+    def run(problems):
+        text = "".join(" ".join(str(int(x)) for x in p) + "\n" for p in problems)
+        out = subprocess.run([str(program)], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        return [line == "1" for line in out.split()]
+    return run
+
+
+def test_the_parity_cases_are_taken(taken):
+    assert all(taken([(B, H, Nq, Nk, 64, causal) for B, H, Nq, Nk, _, causal, _ in CASES] + [(26, 16, 256, n, 64, 0) for n in (128, 200, 256)]))
+
+
+# measured with both launches, one clearly ahead
+AHEAD = [(1, 32, 16384, 0), (32, 16, 512, 0), (2, 6, 9984, 0), (4, 16, 2816, 0), (64, 24, 130, 0), (10, 8, 1265, 0), (1, 32, 16384, 1),
+         (5, 8, 6656, 1), (2, 12, 5555, 1), (4, 32, 4096, 1)]
+BEHIND = [(6, 2, 6247, 0), (4, 6, 6016, 0), (13, 32, 384, 0), (26, 6, 1664, 0), (63, 6, 83, 0), (23, 8, 512, 0), (1, 8, 13184, 1),
+          (12, 32, 476, 1), (29, 24, 640, 1), (1, 2, 256, 0), (1, 8, 3000, 0)]
+
+
+def test_the_rule_follows_the_measurements(taken):
+    got = taken([(B, H, N, N, 64, causal) for B, H, N, causal in AHEAD + BEHIND])
+    assert got == [True] * len(AHEAD) + [False] * len(BEHIND)
+    assert not any(taken([(32, 16, 512, 512, d, 0) for d in (128, 256)]))
+
+
+def test_the_kernel_fits_two_wavefronts_per_simd_without_scratch():
+    kernels = build.resource_usage(build.STAGE_SOURCES)
+    assert len({k["name"] for k in kernels}) == 2 * 4   # element types, causal mask, partial tiles
+    for k in kernels:
+        assert k["vgprs"] + k["agprs"] <= 256 and k["waves_per_simd"] >= 2 and k["scratch_bytes_per_lane"] == 0, k
+        assert 2 * k["lds_bytes_per_workgroup"] <= 160 * 1024, k
