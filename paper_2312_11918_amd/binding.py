@@ -1,7 +1,8 @@
-"""ctypes binding of libfa2's C ABI (see include/fa2.h).  Argument marshalling only.
+"""Binding of libfa2's C ABI (see include/fa2.h).  Argument marshalling only.
 
-``fa2_fwd_raw`` takes raw device addresses; ``fa2_fwd`` takes torch CUDA tensors, which are used
-purely as owners of device memory (``data_ptr()``) and of the current HIP stream.
+``fa2_fwd_raw`` takes raw device addresses, through ctypes; ``fa2_fwd`` takes torch CUDA tensors, which are used
+purely as owners of device memory (``data_ptr()``) and of the current HIP stream: through ``_fa2_torch`` in the common
+case (plain tensors of the current device, its current stream), through ctypes otherwise.
 """
 from __future__ import annotations
 
@@ -25,7 +26,9 @@ FA2_SPLIT_MIN_KEYS = 512
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libfa2.so")
 _PROBE_PATH = os.path.join(_PKG, "libfa2_probe.so")
+_TORCH_PATH = os.path.join(_PKG, "_fa2_torch.so")
 _lib = None
+_forward = None
 _probe = None
 
 
@@ -69,6 +72,25 @@ def load_library():
         lib.fa2_version.restype = ci
         _lib = lib
     return _lib
+
+
+def _load_forward():
+    """``forward`` of _fa2_torch.so (csrc/fa2_torch.cpp).  A missing library is an error."""
+    global _forward
+    if _forward is None:
+        import importlib.machinery
+        import importlib.util
+
+        import torch  # noqa: F401  (its libraries are the extension's)
+
+        load_library()
+        if not os.path.exists(_TORCH_PATH):
+            raise FileNotFoundError(f"{_TORCH_PATH} is not built; run `python -m paper_2312_11918_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_fa2_torch", _TORCH_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_fa2_torch", _TORCH_PATH, loader=loader))
+        loader.exec_module(module)
+        _forward = module.forward
+    return _forward
 
 
 def probe_library_path() -> str:
@@ -162,10 +184,7 @@ def _kept_by_a_graph(torch, tensor) -> bool:
 
 
 def _launch(torch, q, k, v, out, lse, scale, dtype, stream, variant, causal) -> int:
-    """The call into the library for checked tensors of the current device; returns the C return code.
-
-    The host side bounds a small problem: B1 H2 N256 d64 took 13.7 us a call with a device guard around every call and
-    torch's current stream wrapped in a Stream object, 9.9 us without the two; its kernel takes 5.8 us."""
+    """The call into the library for checked tensors of the current device; returns the C return code."""
     B, N, H, d = q.shape
     Nk = k.shape[1]
     handle = torch._C._cuda_getCurrentRawStream(q.device.index) if stream is None else stream.cuda_stream
@@ -207,6 +226,12 @@ def fa2_fwd(q, k, v, scale: float, out=None, lse=None, return_lse: bool = True, 
     ``out`` and ``lse`` given too (not in a capture begun without torch); ``fa2_fwd_qk_raw`` allocates nothing, and
     ``fa2_fwd_ws_raw`` uses the caller's scratch.
     """
+    if stream is None and variant == FA2_VARIANT_AUTO:
+        result = (_forward or _load_forward())(q, k, v, scale, out, lse, return_lse, causal)
+        if result.__class__ is tuple:
+            return result
+        if result is not None:
+            raise Fa2Error(result, fa2_strerror(result))
     import torch
 
     if not (q.is_cuda and k.is_cuda and v.is_cuda):

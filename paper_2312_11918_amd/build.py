@@ -13,6 +13,8 @@ SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query
 STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64, 64 query rows per wavefront
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
+TORCH_SOURCE = os.path.join(_PKG, "csrc", "fa2_torch.cpp")           # the Python call on torch tensors
+TORCH_LIBRARY = os.path.join(_PKG, "_fa2_torch.so")
 PROBE_SOURCES = [os.path.join(_PKG, "csrc", "mfma_probe.hip")]
 PROBE_LIBRARY = os.path.join(_PKG, "libfa2_probe.so")
 
@@ -36,9 +38,32 @@ def _hipcc(sources, library, verbose):
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` next to this file; returns the former's path."""
+    """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` and the call on torch tensors, which uses the former, into
+    ``_fa2_torch.so``, next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
-    return _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES], LIBRARY, verbose)
+    _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES], LIBRARY, verbose)
+    _build_torch_call(verbose)
+    return LIBRARY
+
+
+def _build_torch_call(verbose):
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [INCLUDE, *cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-isystem{p}" for p in includes), TORCH_SOURCE,
+           "-o", TORCH_LIBRARY, f"-L{_PKG}", "-l:libfa2.so", f"-L{torch_lib}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           f"-L{os.path.join(rocm, 'lib')}", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout)
 
 
 def resource_usage(sources=SOURCES):
