@@ -10,7 +10,7 @@ _ROOT = os.path.dirname(_PKG)
 SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile kernels and the C ABI
 SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query per sequence, keys split
                  os.path.join(_PKG, "csrc", "fa2_split.hip")]        # few query tiles, keys split
-STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64, 64 query rows per wavefront
+STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64 and 256, softmax mixed into the MFMAs
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
 TORCH_SOURCE = os.path.join(_PKG, "csrc", "fa2_torch.cpp")           # the Python call on torch tensors
@@ -104,10 +104,10 @@ def resource_usage(sources=SOURCES):
             k["name"] = (f"fa2_fwd_kernel<{'fp16' if dt == 0 else 'bf16'}, d={d}, {wv} wavefronts, {nbuf} LDS buffers"
                          f"{', causal' if causal else ''}{', partial tiles' if ragged else ''}{', keys cut' if cut else ''}>")
             continue
-        m = re.search(r"fa2_stage_kernelILi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
+        m = re.search(r"fa2_stage_kernelILi(\d+)ELi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
         if m:
-            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d=64{', causal' if m[2] == '1' else ''}"
-                         f"{', partial tiles' if m[3] == '1' else ''}>")
+            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}{', causal' if m[3] == '1' else ''}"
+                         f"{', partial tiles' if m[4] == '1' else ''}>")
             continue
         m = re.search(r"(fa2_(?:decode|decode_merge|split_merge)_kernel)ILi(\d+)ELi(\d+)E(?:Lb(\d)E)?", k["mangled"])
         if m:

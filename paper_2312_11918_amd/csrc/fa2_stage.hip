@@ -1,4 +1,4 @@
-// Attention at d = 64 with 64 query rows per wavefront and the softmax mixed into the MFMAs.
+// Attention with the softmax mixed into the MFMAs: d = 64 with 64 query rows per wavefront, and d = 256.
 //
 // At d = 64 the softmax costs a SIMD more issue cycles than the matrix products: per 64 x 64 tile of S and wavefront 224
 // vector instructions (1296 cycles, the exponentials at half rate) against 32 MFMAs (1024 cycles).  Two things kept the tile
@@ -17,7 +17,16 @@
 // 2234 / 2055, B8 H32 N2048 304 / 278, B16 H32 N1024 166 / 156, B32 H16 N512 50.1 / 48.6, B8 H16 N2047 154 / 148, causal B1 H32
 // N16384 1160 / 1054, B8 H32 N2048 182 / 175.
 //
-// Tried and not kept: eight wavefronts (512 rows) per workgroup, level at N = 16384, 4...8 % slower below; two wavefronts (128
+// At d = 256 O^T alone takes half of the 512 registers that the only wavefront of a SIMD has, so a wavefront owns one group of 32
+// rows, and a stage is GEMM-I of S(s+1), then GEMM-II with P~(s-1), one element of the softmax of S(s) after every second MFMA.  The
+// tile kernel's wavefront has nobody to overlap its softmax with.  Bound by the LDS: one fragment per MFMA of four wavefronts and the
+// refills are 43 cycles of it per 32-cycle MFMA, of about 52 that pass at 1.65 GHz.  us before and after: B4 H8 N4095 603 / 561,
+// B6 H12 N1000 122 / 111, B11 H8 N777 104 / 92, B2 H16 N1024 41.0 / 39.2, B9 H24 Nq3 Nk355 20.6 / 18.8; causal B4 H32 N1116 157 / 134,
+// B9 H8 N2709 420 / 344.  It makes no difference there: 6, 12 or 16 fragments in flight instead of 8 (0...-2 %), the two products
+// mixed (0...-1 %), the refills spread over a stage (-1...+1 %).  d = 128 in this form (two groups, one wavefront per SIMD): 6...16 %
+// slower than the tile kernel, which has two.
+//
+// Tried and not kept at d = 64: eight wavefronts (512 rows) per workgroup, level at N = 16384, 4...8 % slower below; two wavefronts (128
 // rows), 6...11 % slower (the K/V refill doubles); one group of rows and three wavefronts per SIMD, 4...9 % slower; four
 // K/V buffers instead of two, 0...-4 %; alternating priorities of the two workgroups of a CU, 0...-1 %.
 #include "fa2_stage_plan.h"
@@ -26,15 +35,8 @@
 namespace fa2 {
 namespace {
 
-constexpr int kD = 64;
-constexpr int kGroups = 2;                            // groups of 32 query rows per wavefront
-constexpr int kWaveRows = 32 * kGroups;
-constexpr int kStageRows = kWaveRows * kWaves;        // query rows per workgroup
 constexpr int kStageKeys = 32;                        // keys per stage, half a K/V tile
-constexpr int kKSteps = kD / 16;                      // MFMA steps along d of GEMM-I: fragments of K per stage
-constexpr int kDBlocks = kD / 32;                     // 32-row blocks of O^T
-constexpr int kVFrags = kStageKeys / 16 * kDBlocks;   // fragments of V per stage
-constexpr int kLoads = Tile<kD>::kLoadsPerWave;       // 1 KiB wavefront loads per tile and wavefront
+constexpr int groups_of(int d) { return d == 64 ? 2 : 1; }   // groups of 32 query rows per wavefront
 constexpr float kSumLimit = 256.0f;                   // a partial row sum beyond 2^kLazyLog2 moves the reference point
 
 template <int N> using Int = std::integral_constant<int, N>;
@@ -44,13 +46,20 @@ template <int N> using Int = std::integral_constant<int, N>;
 //
 // kCausal: one Q tile per workgroup, the longest first.  kRagged: any Nq and Nk, as in fa2_fwd_kernel, but the count of K/V
 // tiles is not padded: a wavefront runs the tiles that its own rows see and only keeps the boundaries of the others.
-template <int DT, bool kCausal, bool kRagged>
-__global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+template <int DT, int kD, bool kCausal, bool kRagged>
+__global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                                                                   const uint16_t* __restrict__ V, uint16_t* __restrict__ O,
                                                                   float* __restrict__ LSE, int H, int Nq, int Nk,
                                                                   float scale_log2e, int n_qtiles, int total) {
   using E = Elem<DT>;
   using T = Tile<kD>;
+  constexpr int kGroups = groups_of(kD);
+  constexpr int kWaveRows = 32 * kGroups;
+  constexpr int kStageRows = kWaveRows * kWaves;        // query rows per workgroup
+  constexpr int kKSteps = kD / 16;                      // MFMA steps along d of GEMM-I: fragments of K per stage
+  constexpr int kDBlocks = kD / 32;                     // 32-row blocks of O^T
+  constexpr int kVFrags = kStageKeys / 16 * kDBlocks;   // fragments of V per stage
+  constexpr int kLoads = T::kLoadsPerWave;              // 1 KiB wavefront loads per tile and wavefront
   using std::false_type;
   using std::true_type;
 
@@ -171,11 +180,23 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
       for (int v = 0; v < 16; ++v)
         if (8 * (v / 4) + (v % 4) > visible + (kCausal ? 32 * g : 0)) s[g][v] = -INFINITY;
   };
+  // Element v of S for the softmax.  At d = 256 S is in accumulation registers and is read where it is needed (the compiler reads
+  // all of it at the start of a stage).  It does not see that this reads what MFMAs wrote: 16 others stand between.
+  auto logit = [&](const f32x16& s, int v) __attribute__((always_inline)) {
+    if constexpr (kD == 64) {
+      return s[v];
+    } else {
+      float x;
+      asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(s[v]));
+      return x;
+    }
+  };
   // Row maximum of the logits of one group that a lane holds in `s` (without its partner in the other half of the wavefront).
   auto lane_max = [&](f32x16& s) __attribute__((always_inline)) {
     // The wait states that the inline maxima need after an MFMA that wrote S; S goes through the asm, or the maxima could be
     // scheduled before it (a maximum of unfinished sums is still a valid reference, but not the same one in every run).
-    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(s));
+    if constexpr (kD == 64) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(s));
+    else asm volatile("s_nop 15\n\ts_nop 3" : "+a"(s));
     float mx = max2_raw(s[0], s[1]);
 #pragma unroll
     for (int v = 2; v < 16; v += 2) mx = max3_raw(mx, s[v], s[v + 1]);
@@ -187,7 +208,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
     return fmaxf(max_with_partner_half_raw(mx) * scale_log2e, kLowest);
   };
 
-  // One stage (parity x): GEMM-II with pf[1 - x] and the V half tile `vt`, mixed with the softmax of st[x][0] -> pf[x][0], then
+  // One stage (parity x), two groups: GEMM-II with pf[1 - x] and the V half tile `vt`, mixed with the softmax of st[x][0] -> pf[x][0], then
   // GEMM-I of the K half tile `kt` -> st[1 - x], mixed with the softmax of st[x][1].  In this order S of group 0 is dead
   // when GEMM-I writes its successor (all at once would take 40 registers too many), and that successor, which the next
   // stage needs first, is done four MFMAs before this stage ends.  The first stage has neither product, the last no GEMM-I.
@@ -195,15 +216,19 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
       __attribute__((always_inline)) {
     constexpr int x = decltype(x_tag)::value;
     constexpr bool kGemm1 = decltype(gemm1_tag)::value, kGemm2 = decltype(gemm2_tag)::value;
-    constexpr int kN2 = kGemm2 ? kVFrags : 0, kFrags = kN2 + (kGemm1 ? kKSteps : 0);
-    constexpr int kRing = 4;   // fragments in flight
-    static_assert(kKSteps == kRing, "the K fragments are all held, for the second group");
-    auto frag = [&](int f) __attribute__((always_inline)) -> u32x4 { return f < kN2 ? v_frag(vt, f) : k_frag(kt, f - kN2); };
+    constexpr int kN1 = kGemm1 ? kKSteps : 0, kN2 = kGemm2 ? kVFrags : 0, kFrags = kN1 + kN2;
+    constexpr int kRing = kGroups == 2 ? 4 : 8;   // fragments in flight
+    static_assert(kGroups == 1 || kKSteps == kRing, "the K fragments are all held, for the second group");
+    // two groups: those of V first; one group: those of K
+    auto frag = [&](int f) __attribute__((always_inline)) -> u32x4 {
+      if constexpr (kGroups == 2) return f < kN2 ? v_frag(vt, f) : k_frag(kt, f - kN2);
+      else return f < kN1 ? k_frag(kt, f) : v_frag(vt, f - kN1);
+    };
     u32x4 ring[kRing];
 #pragma unroll
     for (int f = 0; f < (kFrags < kRing ? kFrags : kRing); ++f) ring[f] = frag(f);
 
-    // The softmax of one group, a pair of elements after each of the 8 MFMAs that `mfma` issues: the exponents of the next
+    // The softmax of one group, a pair of elements after each of the 8 MFMAs that `mfma` issues (one group: over four): the exponents of the next
     // pair, the exponentials of this one, sum and P~ of the last one.  Each part is pinned where it stands; left free, the
     // compiler moves all of it behind the MFMAs, to the first use of P~.
     auto softmax = [&](auto g_tag, auto mfma) __attribute__((always_inline)) {
@@ -211,7 +236,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
       float e[2][2], p[2][2], sum[2];
       auto exponents = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) e[n & 1][i] = __builtin_fmaf(st[x][g][2 * n + i], scale_log2e, -mc_ref[g]);
+        for (int i = 0; i < 2; ++i) e[n & 1][i] = __builtin_fmaf(logit(st[x][g], 2 * n + i), scale_log2e, -mc_ref[g]);
         asm volatile("" : "+v"(e[n & 1][0]), "+v"(e[n & 1][1]));
       };
       auto add_and_pack = [&](int n) __attribute__((always_inline)) {
@@ -225,14 +250,30 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
       __builtin_amdgcn_sched_barrier(0);
       static_for<8>([&](auto n_tag) __attribute__((always_inline)) {
         constexpr int n = decltype(n_tag)::value;
-        mfma(n_tag);
-        if constexpr (n + 1 < 8) exponents(n + 1);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        auto exponential = [&](int i) __attribute__((always_inline)) {
           p[n & 1][i] = __builtin_amdgcn_exp2f(e[n & 1][i]);
           asm volatile("" : "+v"(p[n & 1][i]));
+        };
+        if constexpr (kGroups == 2) {
+          mfma(n_tag);
+          if constexpr (n + 1 < 8) exponents(n + 1);
+          exponential(0);
+          exponential(1);
+          if constexpr (n > 0) add_and_pack(n - 1);
+        } else {
+          static_assert(kKSteps + kVFrags == 4 * 8);
+          mfma(Int<4 * n>{});
+          if constexpr (n + 1 < 8) exponents(n + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma(Int<4 * n + 1>{});
+          exponential(0);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma(Int<4 * n + 2>{});
+          exponential(1);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma(Int<4 * n + 3>{});
+          if constexpr (n > 0) add_and_pack(n - 1);
         }
-        if constexpr (n > 0) add_and_pack(n - 1);
         __builtin_amdgcn_sched_barrier(0);
       });
       add_and_pack(7);
@@ -273,18 +314,32 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
       }
       __builtin_amdgcn_sched_barrier(0);
     };
-    // fragment f for both groups, then the one kRing ahead into its place
-    softmax(Int<0>{}, [&](auto m) __attribute__((always_inline)) {
-      constexpr int f = decltype(m)::value / kGroups, g = decltype(m)::value % kGroups;
-      if constexpr (kGemm2) {
-        ot[g][f % kDBlocks] = E::mfma(ring[f], pf[1 - x][g][f / kDBlocks], ot[g][f % kDBlocks]);
-        if constexpr (g == kGroups - 1 && f + kRing < kFrags) ring[f] = frag(f + kRing);
-      }
-    });
-    softmax(Int<1>{}, [&](auto m) __attribute__((always_inline)) {
-      constexpr int ks = decltype(m)::value % kKSteps, g = decltype(m)::value / kKSteps;
-      if constexpr (kGemm1) st[1 - x][g] = E::mfma(ring[ks], qf[g][ks], ks == 0 ? zeros() : st[1 - x][g]);
-    });
+    if constexpr (kGroups == 2) {
+      // fragment f for both groups, then the one kRing ahead into its place
+      softmax(Int<0>{}, [&](auto m) __attribute__((always_inline)) {
+        constexpr int f = decltype(m)::value / kGroups, g = decltype(m)::value % kGroups;
+        if constexpr (kGemm2) {
+          ot[g][f % kDBlocks] = E::mfma(ring[f], pf[1 - x][g][f / kDBlocks], ot[g][f % kDBlocks]);
+          if constexpr (g == kGroups - 1 && f + kRing < kFrags) ring[f] = frag(f + kRing);
+        }
+      });
+      softmax(Int<1>{}, [&](auto m) __attribute__((always_inline)) {
+        constexpr int ks = decltype(m)::value % kKSteps, g = decltype(m)::value / kKSteps;
+        if constexpr (kGemm1) st[1 - x][g] = E::mfma(ring[ks], qf[g][ks], ks == 0 ? zeros() : st[1 - x][g]);
+      });
+    } else {
+      softmax(Int<0>{}, [&](auto m) __attribute__((always_inline)) {
+        constexpr int i = decltype(m)::value;
+        constexpr bool kFirst = i < kKSteps;
+        constexpr int n = i - kKSteps;   // of GEMM-II
+        if constexpr (kFirst ? kGemm1 : kGemm2) {
+          constexpr int f = kGemm1 ? i : n;
+          if constexpr (kFirst) st[1 - x][0] = E::mfma(ring[f % kRing], qf[0][i], i == 0 ? zeros() : st[1 - x][0]);
+          else ot[0][n % kDBlocks] = E::mfma(ring[f % kRing], pf[1 - x][0][n / kDBlocks], ot[0][n % kDBlocks]);
+          if constexpr (f + kRing < kFrags) ring[f % kRing] = frag(f + kRing);
+        }
+      });
+    }
   };
 
   constexpr int kWaitLoads = 0x0F70;         // s_waitcnt vmcnt(0)
@@ -293,7 +348,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
   const int k_tiles = (Nk + kBc - 1) / kBc;
   const int n_tiles = kCausal ? min((qt + 1) * (kStageRows / kBc), k_tiles) : k_tiles;   // of the workgroup
   // of this wavefront's rows (none if they all lie past the last query)
-  const int n_my = kRagged && row_first >= Nq ? 0 : kCausal ? min(row_first / kBc + kWaveRows / kBc, n_tiles) : n_tiles;
+  const int n_my = kRagged && row_first >= Nq ? 0 : kCausal ? min((row_first + kWaveRows - 1) / kBc + 1, n_tiles) : n_tiles;
 
   stage_in(true_type{}, 0, k_lds0);
 #pragma unroll
@@ -413,24 +468,26 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fa2_stage_kernel(const uint16_
   }
 }
 
-template <int DT, bool kCausal, bool kRagged> int launch(const Problem& p) {
+template <int DT, int kD, bool kCausal, bool kRagged> int launch(const Problem& p) {
+  constexpr int kStageRows = 32 * groups_of(kD) * kWaves;
   const int n_q = (p.Nq + kStageRows - 1) / kStageRows, total = p.B * p.H * n_q;
-  return enqueue(fa2_stage_kernel<DT, kCausal, kRagged>, total, kWaves * 64, p.stream, static_cast<const uint16_t*>(p.Q),
+  return enqueue(fa2_stage_kernel<DT, kD, kCausal, kRagged>, total, kWaves * 64, p.stream, static_cast<const uint16_t*>(p.Q),
                  static_cast<const uint16_t*>(p.K), static_cast<const uint16_t*>(p.V), static_cast<uint16_t*>(p.O), p.LSE, p.H,
                  p.Nq, p.Nk, p.scale_log2e, n_q, total);
 }
 
-template <int DT> int launch(const Problem& p) {
-  const bool ragged = p.Nq % kStageRows != 0 || p.Nk % kBc != 0;
-  return p.causal ? (ragged ? launch<DT, true, true>(p) : launch<DT, true, false>(p))
-                  : (ragged ? launch<DT, false, true>(p) : launch<DT, false, false>(p));
+template <int DT, int kD> int launch(const Problem& p) {
+  const bool ragged = p.Nq % (32 * groups_of(kD) * kWaves) != 0 || p.Nk % kBc != 0;
+  return p.causal ? (ragged ? launch<DT, kD, true, true>(p) : launch<DT, kD, true, false>(p))
+                  : (ragged ? launch<DT, kD, false, true>(p) : launch<DT, kD, false, false>(p));
 }
 
 }  // namespace
 
 bool stage_tiles(const Problem& p, int* rc) {
-  if (!stage_accepts(p.B, p.H, p.Nq, p.d, p.causal)) return false;
-  *rc = p.dtype == FA2_FP16 ? launch<FA2_FP16>(p) : launch<FA2_BF16>(p);
+  if (!stage_accepts(p.B, p.H, p.Nq, p.Nk, p.d, p.causal)) return false;
+  if (p.d == 64) *rc = p.dtype == FA2_FP16 ? launch<FA2_FP16, 64>(p) : launch<FA2_BF16, 64>(p);
+  else *rc = p.dtype == FA2_FP16 ? launch<FA2_FP16, 256>(p) : launch<FA2_BF16, 256>(p);
   return true;
 }
 

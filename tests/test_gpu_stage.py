@@ -1,5 +1,5 @@
-"""GPU parity of the kernel with 64 query rows per wavefront (d = 64, many Q tiles) against the fp64 CPU oracle on guarded buffers,
-with the tolerances of the other launches, at the edges of its stages (32 keys), tiles (64 keys) and workgroups (256 rows)."""
+"""GPU parity of the kernel with the softmax mixed into the MFMAs (d = 64 with many Q tiles, d = 256) against the fp64 CPU oracle on guarded buffers,
+with the tolerances of the other launches, at the edges of its stages (32 keys), tiles (64 keys) and workgroups (256 or 128 rows)."""
 import numpy as np
 import pytest
 
@@ -27,13 +27,23 @@ CASES = [
     (7, 9, 2049, 2049, "fp16", True, 0.01),      # heads not a multiple of 8; a last Q tile of one row
     (8, 9, 1985, 1985, "fp16", True, 0.0),
 ]
+CASES_256 = [
+    (2, 3, 130, 129, "fp16", False, 0.0),        # an odd count of stages and tiles, a last tile of one key
+    (2, 3, 128, 160, "bf16", False, 0.0),        # the last tile half masked
+    (3, 2, 33, 191, "fp16", False, 0.02),        # wavefronts without a row; the reference point moves
+    (3, 5, 97, 193, "bf16", False, 0.0),         # four tiles, the last of one key
+    (2, 3, 256, 256, "fp16", False, 0.05),       # whole tiles
+    (2, 3, 2, 255, "fp16", False, 0.0),
+    (4, 21, 1537, 1537, "fp16", True, 0.01),     # odd counts of Q tiles, the last of one row; heads not a multiple of 8
+    (8, 8, 2176, 2176, "bf16", True, 0.0),       # whole tiles, heads in groups
+]
 
 
-@pytest.mark.parametrize("B,H,Nq,Nk,dtype,causal,outliers", CASES)
-def test_stage_parity(B, H, Nq, Nk, dtype, causal, outliers):
-    print(f"stage case B={B} H={H} Nq={Nq} Nk={Nk} {dtype} causal={causal}", flush=True)
-    qb, kb, vb = _make(B, H, Nq, Nk, 64, dtype, 47000 + Nq + Nk, outliers)
-    scale = 0.125
+@pytest.mark.parametrize("d,B,H,Nq,Nk,dtype,causal,outliers", [(64, *c) for c in CASES] + [(256, *c) for c in CASES_256])
+def test_stage_parity(d, B, H, Nq, Nk, dtype, causal, outliers):
+    print(f"stage case d={d} B={B} H={H} Nq={Nq} Nk={Nk} {dtype} causal={causal}", flush=True)
+    qb, kb, vb = _make(B, H, Nq, Nk, d, dtype, 47000 + Nq + Nk, outliers)
+    scale = d ** -0.5
     o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale, causal=causal)
     o, lse = _run(qb, kb, vb, dtype, scale, causal)
     _check(o, lse, o_ref, lse_ref, "stage")

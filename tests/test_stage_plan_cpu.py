@@ -1,11 +1,11 @@
-"""Which problems run with 64 query rows per wavefront, and the compiled form of that kernel, on the CPU."""
+"""Which problems run with the softmax mixed into the MFMAs, and the compiled form of that kernel, on the CPU."""
 import os
 import subprocess
 
 import pytest
 
 from paper_2312_11918_amd import build
-from test_gpu_stage import CASES
+from test_gpu_stage import CASES, CASES_256
 
 PROGRAM = r"""
 #include <stdio.h>
@@ -13,7 +13,7 @@ PROGRAM = r"""
 int main() {
   int B, H, Nq, Nk, d, causal;
   while (scanf("%d %d %d %d %d %d", &B, &H, &Nq, &Nk, &d, &causal) == 6)
-    printf("%d\n", fa2::stage_accepts(B, H, Nq, d, causal != 0) && !fa2::split_plan(B, H, Nq, Nk, d, causal != 0, true).use);
+    printf("%d\n", fa2::stage_accepts(B, H, Nq, Nk, d, causal != 0) && !fa2::split_plan(B, H, Nq, Nk, d, causal != 0, true).use);
 }
 """
 
@@ -34,6 +34,7 @@ def taken(tmp_path_factory):
 
 
 def test_the_parity_cases_are_taken(taken):
+    assert all(taken([(B, H, Nq, Nk, 256, causal) for B, H, Nq, Nk, _, causal, _ in CASES_256]))
     assert all(taken([(B, H, Nq, Nk, 64, causal) for B, H, Nq, Nk, _, causal, _ in CASES] + [(26, 16, 256, n, 64, 0) for n in (128, 200, 256)]))
 
 
@@ -43,16 +44,24 @@ AHEAD = [(1, 32, 16384, 0), (32, 16, 512, 0), (2, 6, 9984, 0), (4, 16, 2816, 0),
 BEHIND = [(6, 2, 6247, 0), (4, 6, 6016, 0), (13, 32, 384, 0), (26, 6, 1664, 0), (63, 6, 83, 0), (23, 8, 512, 0), (1, 8, 13184, 1),
           (12, 32, 476, 1), (29, 24, 640, 1), (1, 2, 256, 0), (1, 8, 3000, 0)]
 
+AHEAD_256 = [(4, 8, 4095, 0), (6, 12, 1000, 0), (11, 8, 777, 0), (2, 16, 1024, 0), (27, 6, 768, 0), (2, 6, 2048, 0), (9, 8, 2709, 1),
+             (2, 24, 3633, 1), (8, 8, 2816, 1)]
+BEHIND_256 = [(32, 16, 512, 0), (16, 16, 1024, 0), (4, 8, 4096, 0), (17, 24, 74, 0), (8, 16, 2048, 1), (32, 16, 512, 1), (7, 32, 768, 1),
+              (1, 16, 4096, 1), (3, 6, 3328, 1)]
+
 
 def test_the_rule_follows_the_measurements(taken):
     got = taken([(B, H, N, N, 64, causal) for B, H, N, causal in AHEAD + BEHIND])
     assert got == [True] * len(AHEAD) + [False] * len(BEHIND)
     assert not any(taken([(32, 16, 512, 512, d, 0) for d in (128, 256)]))
+    got = taken([(B, H, N, N, 256, causal) for B, H, N, causal in AHEAD_256 + BEHIND_256])
+    assert got == [True] * len(AHEAD_256) + [False] * len(BEHIND_256)
 
 
-def test_the_kernel_fits_two_wavefronts_per_simd_without_scratch():
+def test_the_kernels_fit_their_registers_without_scratch():
     kernels = build.resource_usage(build.STAGE_SOURCES)
-    assert len({k["name"] for k in kernels}) == 2 * 4   # element types, causal mask, partial tiles
+    assert len({k["name"] for k in kernels}) == 2 * 2 * 4   # element types, head dimensions, causal mask, partial tiles
     for k in kernels:
-        assert k["vgprs"] + k["agprs"] <= 256 and k["waves_per_simd"] >= 2 and k["scratch_bytes_per_lane"] == 0, k
-        assert 2 * k["lds_bytes_per_workgroup"] <= 160 * 1024, k
+        per_simd = 2 if "d=64" in k["name"] else 1   # wavefronts; as many workgroups per CU
+        assert per_simd * (k["vgprs"] + k["agprs"]) <= 512 and k["waves_per_simd"] >= per_simd, k
+        assert k["scratch_bytes_per_lane"] == 0 and per_simd * k["lds_bytes_per_workgroup"] <= 160 * 1024, k
