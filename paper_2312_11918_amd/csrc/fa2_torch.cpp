@@ -74,7 +74,10 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
       Py_RETURN_NONE;
   }
   const double scale = PyFloat_AsDouble(args[3]);
-  if (scale == -1.0 && PyErr_Occurred()) return nullptr;
+  if (scale == -1.0 && PyErr_Occurred()) {   // float() takes more than this, a text for instance
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
 
   const hipStream_t stream = c10::hip::getCurrentHIPStream(device.index()).stream();
   const int mask = causal ? FA2_MASK_CAUSAL : FA2_MASK_NONE;

@@ -66,6 +66,8 @@ def test_what_it_leaves_to_the_python_path():
     with torch.device("cuda"):   # a torch function mode
         assert _native(q, k, v, *rest) is None
         assert torch.equal(fa2.fa2_fwd(q, k, v, 0.125)[0], ref)
+    assert _native(q, k, v, "0.125", *rest[1:]) is None   # a scale that only float() reads
+    assert torch.equal(fa2.fa2_fwd(q, k, v, "0.125")[0], ref)
     bad = [((q.cpu(), k, v), {}), ((q.float(), k, v), {}), ((q, k.bfloat16(), v), {}), ((q[0], k, v), {}), ((q, k, v[:, :64]), {}),
            ((q.transpose(1, 2).contiguous().transpose(1, 2), k, v), {}), ((q, k, v), {"out": q[:, :64].contiguous()}),
            ((q, k, v), {"out": torch.empty_like(q, dtype=torch.float32)}), ((q, k, v), {"lse": ref_lse.half()}),
