@@ -19,8 +19,8 @@
 //
 // At d = 256 O^T alone takes half of the 512 registers that the only wavefront of a SIMD has, so a wavefront owns one group of 32
 // rows, and a stage is GEMM-I of S(s+1), then GEMM-II with P~(s-1), one element of the softmax of S(s) after every second MFMA.  The
-// tile kernel's wavefront has nobody to overlap its softmax with.  Bound by the LDS: one fragment per MFMA of four wavefronts and the
-// refills are 43 cycles of it per 32-cycle MFMA, of about 52 that pass at 1.65 GHz.  us before and after: B4 H8 N4095 603 / 561,
+// tile kernel's wavefront has nobody to overlap its softmax with.  An MFMA, 32 cycles, takes about 68 (34 ns at 2.0 GHz); the LDS is
+// busy for 43 of them, with one fragment per MFMA of four wavefronts and the refills.  What the rest goes to is not known.  us before and after: B4 H8 N4095 603 / 561,
 // B6 H12 N1000 122 / 111, B11 H8 N777 104 / 92, B2 H16 N1024 41.0 / 39.2, B9 H24 Nq3 Nk355 20.6 / 18.8; causal B4 H32 N1116 157 / 134,
 // B9 H8 N2709 420 / 344.  It makes no difference there: 6, 12 or 16 fragments in flight instead of 8 (0...-2 %), the two products
 // mixed (0...-1 %), the refills spread over a stage (-1...+1 %).  d = 128 in this form (two groups, one wavefront per SIMD): 6...16 %
