@@ -279,13 +279,15 @@ __global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kerne
       add_and_pack(7);
       // A P~ beyond the limit shows in the row's partial sums (of either half of the wavefront).  Then the reference of that
       // row moves, O and its sums are rescaled, and the stage's exponentials are taken again; S is still there, and so far
-      // no product has used P~.
+      // no product has used P~.  The reference only rises: the sums may hold the first half's, and the limit be passed by
+      // keys far below it (falling with them, by up to 2^15 a tile, O and l would leave fp32; a row whose keys here are all at
+      // or below its reference has P~ <= 1 and stays).
       if (__builtin_amdgcn_ballot_w64(sum[0] + sum[1] > kSumLimit) != 0) {
         const uint32_t u = __builtin_bit_cast(uint32_t, sum[0] + sum[1]);
         const auto both = __builtin_amdgcn_permlane32_swap(u, u, false, false);
         const bool move = __builtin_bit_cast(float, (uint32_t)both[0]) > kSumLimit ||
                           __builtin_bit_cast(float, (uint32_t)both[1]) > kSumLimit;
-        const float to = reference(lane_max(st[x][g]));
+        const float to = fmaxf(mc_ref[g], reference(lane_max(st[x][g])));
         // a row that stays gets exactly 1: its bits must not depend on the other rows of the wavefront
         const float alpha = move ? __builtin_amdgcn_exp2f(mc_ref[g] - to) : 1.0f;
         if (move) mc_ref[g] = to;

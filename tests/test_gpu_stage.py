@@ -84,3 +84,41 @@ def test_a_rows_bits_do_not_depend_on_its_neighbours():
     order = np.random.Generator(np.random.PCG64(3)).permutation(N)
     o2, lse2 = _run(qb[:, order].copy(), kb, vb, "fp16", 0.125)
     assert np.array_equal(o[:, order], o2) and np.array_equal(lse[:, :, order], lse2)
+
+
+# B, H, Nq, Nk, d, dtype, causal: 12 tiles and more of keys that drive the reference point (test_stage_plan_cpu.py: all staged).  bf16
+# only where P = 1 and 2^8 and few heads keep |O| below 4, half an ulp of which is 7.8e-3.
+SINKING = [
+    (26, 16, 256, 768, 64, "fp16", False),
+    (26, 16, 250, 801, 64, "fp16", False),
+    (8, 8, 2048, 2048, 64, "fp16", True),
+    (7, 9, 2049, 2049, 64, "fp16", True),
+    (9, 16, 130, 769, 256, "bf16", False),
+    (9, 16, 256, 768, 256, "fp16", False),
+    (4, 21, 1537, 1537, 256, "fp16", True),
+]
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d,dtype,causal", SINKING)
+def test_the_reference_point_never_falls(B, H, Nq, Nk, d, dtype, causal):
+    # Every tile after the first: one key 8 (log2) above a level that sinks by 15 a tile, in the first half, whose sum it brings
+    # to the limit exactly; the second half's keys, 15 below, push it past.  A reference that followed the second half's maximum
+    # would sink with them and O and its sums grow by 2^15 a tile, beyond fp32 after 9.
+    print(f"sinking reference B={B} H={H} Nq={Nq} Nk={Nk} d={d} {dtype} causal={causal}", flush=True)
+    qb, kb, vb = _make(B, H, Nq, Nk, d, dtype, 48000 + Nq + d)
+    logits = np.full(Nk, -225.0)                     # integers that both types hold
+    logits[:64] = 0.0
+    for t in range(1, 12):
+        level = -15.0 * (t - 1)
+        logits[64 * t:64 * t + 32] = level - 60.0
+        logits[64 * t + 3] = level + 8.0
+        logits[64 * t + 32:64 * t + 64] = level - 15.0
+    bits = (lambda x: np.float16(x).view(np.uint16)) if dtype == "fp16" else \
+        (lambda x: (np.float32(x).view(np.uint32) >> 16).astype(np.uint16))
+    qb[...], kb[..., 0] = 0, bits(logits)[None, :, None]
+    qb[..., 0] = bits(1.0)
+    scale = 0.6931472                                # scale * log2(e) is exactly 1 in fp32
+    assert np.float32(scale) * np.float32(1.44269504088896340736) == 1.0
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale, causal=causal)
+    o, lse = _run(qb, kb, vb, dtype, scale, causal)
+    _check(o, lse, o_ref, lse_ref, "sinking reference")
