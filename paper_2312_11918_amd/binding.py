@@ -244,6 +244,8 @@ def fa2_fwd(q, k, v, scale: float, out=None, lse=None, return_lse: bool = True, 
         raise ValueError(f"unsupported element type {q.dtype}")
     if k.dtype != q.dtype or v.dtype != q.dtype:
         raise ValueError("q, k, v must share one element type")
+    if k.device != q.device or v.device != q.device:   # (the kernel would follow any address)
+        raise ValueError("q, k, v must be on one device")
     if (q.dim() != 4 or k.dim() != 4 or v.shape != k.shape or k.shape[0] != q.shape[0] or k.shape[2:] != q.shape[2:]):
         raise ValueError(f"q must be [B, Nq, H, d], k and v [B, Nk, H, d]; got {tuple(q.shape)}, {tuple(k.shape)}, "
                          f"{tuple(v.shape)}")
@@ -257,8 +259,9 @@ def fa2_fwd(q, k, v, scale: float, out=None, lse=None, return_lse: bool = True, 
     if return_lse:
         if lse is None:
             lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-        elif tuple(lse.shape) != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
-            raise ValueError("lse must be a contiguous fp32 [B, H, N] tensor")
+        elif (tuple(lse.shape) != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous() or
+              lse.device != q.device):
+            raise ValueError("lse must be a contiguous fp32 [B, H, N] tensor on the device of q")
     else:
         lse = None
     index = q.device.index

@@ -71,7 +71,8 @@ def test_what_it_leaves_to_the_python_path():
     bad = [((q.cpu(), k, v), {}), ((q.float(), k, v), {}), ((q, k.bfloat16(), v), {}), ((q[0], k, v), {}), ((q, k, v[:, :64]), {}),
            ((q.transpose(1, 2).contiguous().transpose(1, 2), k, v), {}), ((q, k, v), {"out": q[:, :64].contiguous()}),
            ((q, k, v), {"out": torch.empty_like(q, dtype=torch.float32)}), ((q, k, v), {"lse": ref_lse.half()}),
-           ((q, k, v), {"lse": ref_lse[:, :, ::2]})]
+           ((q, k, v), {"lse": ref_lse[:, :, ::2]}), ((q, k, v), {"lse": ref_lse.cpu()}), ((q, k.cpu(), v), {}), ((q, k, v.cpu()), {}),
+           ((q, k, v), {"out": ref.cpu()})]
     for tensors, kw in bad:
         assert _native(*tensors, 0.125, kw.get("out"), kw.get("lse"), True, False) is None
         with pytest.raises(ValueError):
