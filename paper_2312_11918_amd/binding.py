@@ -75,22 +75,32 @@ def load_library():
 
 
 def _load_forward():
-    """``forward`` of _fa2_torch.so (csrc/fa2_torch.cpp).  A missing library is an error."""
+    """``forward`` of _fa2_torch.so (csrc/fa2_torch.cpp).  Where that library is missing, does not load, or was built for
+    another torch (it uses private headers), every call goes the Python path, which runs the same kernels."""
     global _forward
     if _forward is None:
         import importlib.machinery
         import importlib.util
+        import warnings
 
-        import torch  # noqa: F401  (its libraries are the extension's)
+        import torch  # (its libraries are the extension's)
 
-        load_library()
-        if not os.path.exists(_TORCH_PATH):
-            raise FileNotFoundError(f"{_TORCH_PATH} is not built; run `python -m paper_2312_11918_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("_fa2_torch", _TORCH_PATH)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_fa2_torch", _TORCH_PATH, loader=loader))
-        loader.exec_module(module)
-        _forward = module.forward
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("_fa2_torch", _TORCH_PATH)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_fa2_torch", _TORCH_PATH, loader=loader))
+            loader.exec_module(module)
+            if module.torch_version != torch.__version__:
+                raise ImportError(f"built for torch {module.torch_version}, this is {torch.__version__}")
+            _forward = module.forward
+        except (ImportError, OSError) as e:
+            warnings.warn(f"{_TORCH_PATH}: {e}; fa2_fwd takes a few microseconds more per call without it "
+                          "(`python -m paper_2312_11918_amd.build` builds it)", RuntimeWarning, stacklevel=3)
+            _forward = _leave_to_python
     return _forward
+
+
+def _leave_to_python(*_):
+    return None
 
 
 def probe_library_path() -> str:

@@ -135,4 +135,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fa2_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fa2_torch(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fa2_torch(void) {
+  PyObject* const m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", FA2_TORCH_VERSION) != 0) {   // whose headers these are
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -1,4 +1,4 @@
-"""What fa2_fwd refuses before any launch, without a GPU: stand-ins for device tensors, which have no memory."""
+"""What fa2_fwd refuses before any launch, and what it does without its native call, without a GPU: stand-ins for device tensors, which have no memory."""
 import pytest
 import torch
 
@@ -43,3 +43,31 @@ def test_a_tensor_elsewhere_is_refused_before_a_launch(launches, which, device):
     with pytest.raises(ValueError):
         _call(**{which: device})
     assert not launches
+
+
+def _no_file(monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "_TORCH_PATH", str(tmp_path / "_fa2_torch.so"))
+
+
+def _not_a_library(monkeypatch, tmp_path):
+    (tmp_path / "_fa2_torch.so").write_bytes(b"text")
+    _no_file(monkeypatch, tmp_path)
+
+
+def _other_torch(monkeypatch, tmp_path):
+    monkeypatch.setattr(torch, "__version__", "1.0.0")
+
+
+@pytest.mark.parametrize("lacking", [_no_file, _not_a_library, _other_torch])
+def test_calls_without_the_native_call_go_the_python_path(launches, monkeypatch, tmp_path, lacking):
+    monkeypatch.setattr(binding, "_forward", None)
+    lacking(monkeypatch, tmp_path)
+    with pytest.warns(RuntimeWarning, match="_fa2_torch.so"):
+        _call()
+    _call()   # (says so once)
+    assert len(launches) == 2
+
+
+def test_the_native_call_loads(monkeypatch):
+    monkeypatch.setattr(binding, "_forward", None)
+    assert binding._load_forward() is not binding._leave_to_python
