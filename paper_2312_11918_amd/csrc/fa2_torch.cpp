@@ -36,6 +36,14 @@ bool plain(PyObject* obj) {
          t.has_storage() && t.is_contiguous();
 }
 
+// The interpreter's lock given up for a scope, which an exception may leave.
+struct WithoutGil {
+  PyThreadState* const state = PyEval_SaveThread();
+  WithoutGil() = default;
+  WithoutGil(const WithoutGil&) = delete;
+  ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 // forward(q, k, v, scale, out, lse, return_lse, causal): (O, LSE), or the library's error code, or None
 PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
@@ -86,26 +94,26 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) Py_RETURN_NONE;
   }
-  if (!out.defined()) out = at::empty_like(q);
-  if (return_lse && !lse.defined()) lse = at::empty({B, H, Nq}, q.options().dtype(at::kFloat));
-  // Scratch of the launch stream: dropped on return, its memory is handed out again only behind this call's kernels.  Without
-  // it the call still runs, its keys unsplit.
   at::Tensor workspace;
-  if (bytes != 0) {
-    try {
-      workspace = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
-    } catch (const c10::OutOfMemoryError&) {
-    }
-  }
-  const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
-  void* const op = out.data_ptr();
-  float* const lp = lse.defined() ? static_cast<float*>(lse.data_ptr()) : nullptr;
-  void* const wp = workspace.defined() ? workspace.data_ptr() : nullptr;
   int rc;
-  Py_BEGIN_ALLOW_THREADS   // (a launch waits where the queue is full)
-  rc = fa2_fwd_ws(qp, kp, vp, op, lp, (int)B, (int)H, (int)Nq, (int)Nk, (int)d, (float)scale,
-                  type == at::kHalf ? FA2_FP16 : FA2_BF16, mask, wp, bytes, stream);
-  Py_END_ALLOW_THREADS
+  {
+    // (an allocation waits for the driver at times, a launch where the queue is full)
+    const WithoutGil released;
+    if (!out.defined()) out = at::empty_like(q);
+    if (return_lse && !lse.defined()) lse = at::empty({B, H, Nq}, q.options().dtype(at::kFloat));
+    // Scratch of the launch stream: dropped on return, its memory is handed out again only behind this call's kernels.  Without
+    // it the call still runs, its keys unsplit.
+    if (bytes != 0) {
+      try {
+        workspace = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
+      } catch (const c10::OutOfMemoryError&) {
+      }
+    }
+    rc = fa2_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                    lse.defined() ? static_cast<float*>(lse.data_ptr()) : nullptr, (int)B, (int)H, (int)Nq, (int)Nk, (int)d,
+                    (float)scale, type == at::kHalf ? FA2_FP16 : FA2_BF16, mask,
+                    workspace.defined() ? workspace.data_ptr() : nullptr, bytes, stream);
+  }
   if (rc != FA2_OK) return PyLong_FromLong(rc);
 
   PyObject* const o_obj = args[4] != Py_None ? Py_NewRef(args[4]) : THPVariable_Wrap(out);

@@ -1,5 +1,9 @@
 """The native call of fa2_fwd against its Python path (which a given stream takes): the same bits, results and errors, whichever
 form of tensors, outputs and surroundings decides between the two."""
+import os
+import subprocess
+import sys
+import sysconfig
 import threading
 
 import pytest
@@ -137,3 +141,48 @@ def test_surroundings():
     for t in threads:
         t.join()
     assert results == [True] * 4
+
+
+# Loaded as torch's allocator in a process of its own: whether the thread that allocates holds the interpreter's lock.
+ALLOCATOR = r"""
+#include <Python.h>
+#include <hip/hip_runtime.h>
+static int calls = 0, held = 0;
+extern "C" void* counted_alloc(ssize_t size, int, hipStream_t) {
+  ++calls;
+  held += PyGILState_Check();
+  void* p = nullptr;
+  return hipMalloc(&p, (size_t)size) == hipSuccess ? p : nullptr;
+}
+extern "C" void counted_free(void* p, ssize_t, int, hipStream_t) { (void)hipFree(p); }
+extern "C" int alloc_calls() { return calls; }
+extern "C" int alloc_held() { return held; }
+"""
+ALLOCATING = r"""
+import ctypes, sys
+sys.path.insert(0, sys.argv[2])
+import torch
+allocator = torch.cuda.memory.CUDAPluggableAllocator(sys.argv[1], "counted_alloc", "counted_free")
+torch.cuda.memory.change_current_allocator(allocator)
+from paper_2312_11918_amd import binding
+counts = ctypes.CDLL(sys.argv[1])
+q, k, v = (torch.ones((1, n, 2, 64), device="cuda", dtype=torch.float16) for n in (512, 8192, 8192))
+before = counts.alloc_calls(), counts.alloc_held()
+out = binding._load_forward()(q, k, v, 0.125, None, None, True, False)   # O, LSE and scratch memory
+torch.cuda.synchronize()
+print("calls", counts.alloc_calls() - before[0], "held", counts.alloc_held() - before[1], "o", float(out[0].float().mean()), flush=True)
+del out, q, k, v
+"""
+
+
+def test_other_threads_run_while_it_allocates(tmp_path):
+    # memory from the driver can take long: the interpreter's lock is free meanwhile, as it is in torch's own calls
+    print("torch call: allocations", flush=True)
+    source, library = tmp_path / "counted.cpp", str(tmp_path / "counted.so")
+    source.write_text(ALLOCATOR)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", f"-I{sysconfig.get_paths()['include']}", f"-I{rocm}/include",
+                    str(source), "-o", library, f"-L{rocm}/lib", "-lamdhip64"], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    done = subprocess.run([sys.executable, "-c", ALLOCATING, library, root], stdout=subprocess.PIPE, text=True, timeout=100)
+    assert done.returncode == 0 and done.stdout.split() == ["calls", "3", "held", "0", "o", "1.0"], done
