@@ -23,7 +23,7 @@ CASES = [
     (13, 16, 512, 192, "bf16", False, 0.0),
     (26, 16, 256, 448, "fp16", False, 0.05),     # odd count of tiles; the reference point moves
     (8, 25, 511, 257, "fp16", False, 0.0),
-    (8, 8, 2048, 2048, "bf16", True, 0.0),       # whole tiles; heads in groups
+    (8, 9, 2048, 2048, "bf16", True, 0.0),       # whole tiles; heads in groups
     (7, 9, 2049, 2049, "fp16", True, 0.01),      # heads not a multiple of 8; a last Q tile of one row
     (8, 9, 1985, 1985, "fp16", True, 0.0),
 ]
@@ -91,7 +91,7 @@ def test_a_rows_bits_do_not_depend_on_its_neighbours():
 SINKING = [
     (26, 16, 256, 768, 64, "fp16", False),
     (26, 16, 250, 801, 64, "fp16", False),
-    (8, 8, 2048, 2048, 64, "fp16", True),
+    (8, 9, 2048, 2048, 64, "fp16", True),
     (7, 9, 2049, 2049, 64, "fp16", True),
     (9, 16, 130, 769, 256, "bf16", False),
     (9, 16, 256, 768, 256, "fp16", False),

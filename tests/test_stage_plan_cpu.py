@@ -43,7 +43,12 @@ def test_the_parity_cases_are_taken(taken):
 AHEAD = [(1, 32, 16384, 0), (32, 16, 512, 0), (2, 6, 9984, 0), (4, 16, 2816, 0), (64, 24, 130, 0), (10, 8, 1265, 0), (1, 32, 16384, 1),
          (5, 8, 6656, 1), (2, 12, 5555, 1), (4, 32, 4096, 1)]
 BEHIND = [(6, 2, 6247, 0), (4, 6, 6016, 0), (13, 32, 384, 0), (26, 6, 1664, 0), (63, 6, 83, 0), (23, 8, 512, 0), (1, 8, 13184, 1),
-          (12, 32, 476, 1), (29, 24, 640, 1), (1, 2, 256, 0), (1, 8, 3000, 0)]
+          (12, 32, 476, 1), (29, 24, 640, 1), (1, 2, 256, 0), (1, 8, 3000, 0),
+          (22, 32, 256, 0), (64, 16, 256, 0), (78, 12, 512, 0), (43, 12, 706, 0), (56, 8, 896, 0),   # short: starts and ends count
+          (1, 16, 8036, 1), (2, 16, 4096, 1), (1, 32, 3912, 1), (3, 16, 3968, 1), (2, 32, 2944, 1)]   # pairs of whole rounds
+# B, H, Nq, Nk
+AHEAD_QK = [(22, 8, 3527, 167), (63, 8, 650, 190), (26, 16, 256, 119)]
+BEHIND_QK = [(21, 32, 256, 71), (27, 12, 450, 117), (44, 8, 512, 72), (26, 24, 782, 127), (98, 2, 2644, 384)]
 
 AHEAD_256 = [(4, 8, 4095, 0), (6, 12, 1000, 0), (11, 8, 777, 0), (2, 16, 1024, 0), (27, 6, 768, 0), (2, 6, 2048, 0), (9, 8, 2709, 1),
              (2, 24, 3633, 1), (8, 8, 2816, 1)]
@@ -54,6 +59,8 @@ BEHIND_256 = [(32, 16, 512, 0), (16, 16, 1024, 0), (4, 8, 4096, 0), (17, 24, 74,
 def test_the_rule_follows_the_measurements(taken):
     got = taken([(B, H, N, N, 64, causal) for B, H, N, causal in AHEAD + BEHIND])
     assert got == [True] * len(AHEAD) + [False] * len(BEHIND)
+    got = taken([(B, H, Nq, Nk, 64, 0) for B, H, Nq, Nk in AHEAD_QK + BEHIND_QK])
+    assert got == [True] * len(AHEAD_QK) + [False] * len(BEHIND_QK)
     assert not any(taken([(32, 16, 512, 512, d, 0) for d in (128, 256)]))
     got = taken([(B, H, N, N, 256, causal) for B, H, N, causal in AHEAD_256 + BEHIND_256])
     assert got == [True] * len(AHEAD_256) + [False] * len(BEHIND_256)
