@@ -59,6 +59,25 @@ def test_parity_explicit_variants(B, H, N, d, dtype, variant):
     check(o, lse, o_ref, lse_ref, f"variant {variant} B{B} H{H} N{N} d{d} {dtype}")
 
 
+@pytest.mark.parametrize("B,H,N,dtype", [
+    (1, 2, 128, "fp16"),          # one Q tile, two K/V tiles: no main-loop trip
+    (1, 2, 257, "bf16"),          # partial tiles, the last of one row and one key
+    (2, 1, 321, "fp16"),          # an odd count of K/V tiles, a padding tile beside the last
+    (1, 3, 384, "bf16"),
+    (1, 3, 640, "fp16"),          # whole tiles, several main-loop trips
+    (2, 2, 963, "fp16"),
+])
+def test_parity_explicit_128_rows_d256(B, H, N, dtype):
+    # the automatic choice runs most of these sizes in another kernel
+    seed = 2600 + N
+    print(f"128-row shape case B={B} H={H} N={N} d=256 {dtype} seed={seed}", flush=True)
+    frac = 0.01 if dtype == "fp16" else 0.0
+    qb, kb, vb = workloads.make_qkv(B, N, H, 256, dtype, seed, k_outlier_frac=frac, k_outlier_gain=6.0)
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), 0.0625)
+    o, lse = run_gpu(qb, kb, vb, dtype, 0.0625, fa2.FA2_VARIANT_NARROW)
+    check(o, lse, o_ref, lse_ref, f"128-row shape B{B} H{H} N{N} d256 {dtype}")
+
+
 def test_parity_workload_1_full():
     w, qb, kb, vb = workloads.make_workload(1)
     print(f"workload 1 {w.name} seed={w.seed}", flush=True)

@@ -1,12 +1,13 @@
-"""GPU parity of the kernel with the softmax mixed into the MFMAs (d = 64 with many Q tiles, d = 256) against the fp64 CPU oracle on guarded buffers,
-with the tolerances of the other launches, at the edges of its stages (32 keys), tiles (64 keys) and workgroups (256 or 128 rows)."""
+"""GPU parity of the kernel with the softmax mixed into the MFMAs (d = 64 with many Q tiles, d = 256) against the fp64 CPU
+oracle on guarded buffers, with the tolerances of the other launches, and against the tile kernel bit by bit, at
+the edges of its stages (32 keys), tiles (64 keys) and workgroups (256 or 128 rows)."""
 import numpy as np
 import pytest
 
 import oracle
 import paper_2312_11918_amd as fa2
 from test_gpu_ragged import _check, _make, _run
-from _gpu_common import mask_by_lowest_value
+from _gpu_common import mask_by_lowest_value, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -49,12 +50,15 @@ def test_stage_parity(d, B, H, Nq, Nk, dtype, causal, outliers):
     _check(o, lse, o_ref, lse_ref, "stage")
 
 
-@pytest.mark.parametrize("live", [1, 33, 64, 100])
-def test_keys_masked_by_the_lowest_value(live):
+COMPANY = {64: (26, 16, 256, 200), 256: (2, 3, 130, 200)}   # B, H, Nq, Nk of staged problems
+
+
+@pytest.mark.parametrize("d,live", [(d, n) for d in (64, 256) for n in (1, 33, 64, 100)])
+def test_keys_masked_by_the_lowest_value(d, live):
     # scaled logits of masked keys overflow fp32; O and LSE are those of the live keys, also over stages that hold none
-    print(f"stage masked keys live={live}", flush=True)
-    B, H, Nq, Nk = 26, 16, 256, 200
-    qb, kb, vb = _make(B, H, Nq, Nk, 64, "bf16", 9300 + live)
+    print(f"stage masked keys d={d} live={live}", flush=True)
+    B, H, Nq, Nk = COMPANY[d]
+    qb, kb, vb = _make(B, H, Nq, Nk, d, "bf16", 9300 + live)
     qb, kb = mask_by_lowest_value(qb, kb, live, "bf16")
     o_ref, lse_ref = oracle.attention(oracle.widen(qb, "bf16"), oracle.widen(kb[:, :live].copy(), "bf16"),
                                       oracle.widen(vb[:, :live].copy(), "bf16"), 1.0)
@@ -62,11 +66,12 @@ def test_keys_masked_by_the_lowest_value(live):
     _check(o, lse, o_ref, lse_ref, "masked keys")
 
 
-def test_first_keys_masked_by_the_lowest_value():
-    # the first stage holds no live key: its reference stops at the lowest finite number and moves with the second
-    B, H, Nq, Nk, dead = 26, 16, 256, 128, 40
-    print("stage first keys masked", flush=True)
-    qb, kb, vb = _make(B, H, Nq, Nk, 64, "bf16", 9400)
+@pytest.mark.parametrize("d,dead", [(64, 40), (256, 70)])
+def test_first_keys_masked_by_the_lowest_value(d, dead):
+    # the first stage (d = 256: the first tile) holds no live key: the reference is or stops at the lowest finite number, then moves
+    B, H, Nq, Nk = COMPANY[d]
+    print(f"stage first keys masked d={d}", flush=True)
+    qb, kb, vb = _make(B, H, Nq, Nk, d, "bf16", 9400)
     qb, kb = mask_by_lowest_value(qb, kb[:, ::-1].copy(), Nk - dead, "bf16")
     kb, live = kb[:, ::-1].copy(), slice(dead, None)   # masked keys first
     o_ref, lse_ref = oracle.attention(oracle.widen(qb, "bf16"), oracle.widen(kb[:, live].copy(), "bf16"),
@@ -75,15 +80,37 @@ def test_first_keys_masked_by_the_lowest_value():
     _check(o, lse, o_ref, lse_ref, "first keys masked")
 
 
-def test_a_rows_bits_do_not_depend_on_its_neighbours():
+@pytest.mark.parametrize("d,B,H,N", [(64, 26, 16, 256), (256, 2, 3, 256)])
+def test_a_rows_bits_do_not_depend_on_its_neighbours(d, B, H, N):
     # which rows move their reference is decided from their own values: outlier keys, and the same rows in other company
-    print("stage bits", flush=True)
-    B, H, N = 26, 16, 256
-    qb, kb, vb = _make(B, H, N, N, 64, "fp16", 47777, 0.05)
-    o, lse = _run(qb, kb, vb, "fp16", 0.125)
+    print(f"stage bits d={d}", flush=True)
+    qb, kb, vb = _make(B, H, N, N, d, "fp16", 47777, 0.05)
+    o, lse = _run(qb, kb, vb, "fp16", d ** -0.5)
     order = np.random.Generator(np.random.PCG64(3)).permutation(N)
-    o2, lse2 = _run(qb[:, order].copy(), kb, vb, "fp16", 0.125)
+    o2, lse2 = _run(qb[:, order].copy(), kb, vb, "fp16", d ** -0.5)
     assert np.array_equal(o[:, order], o2) and np.array_equal(lse[:, :, order], lse2)
+
+
+# B, H, N, d, dtype: square, staged (test_stage_plan_cpu.py), whole and partial tiles
+SAME_BITS = [
+    (26, 16, 256, 64, "fp16"),
+    (26, 16, 233, 64, "bf16"),
+    (8, 25, 511, 64, "fp16"),
+    (2, 3, 256, 256, "bf16"),
+    (2, 3, 257, 256, "fp16"),
+    (2, 3, 191, 256, "bf16"),
+]
+
+
+@pytest.mark.parametrize("B,H,N,d,dtype", SAME_BITS)
+def test_the_tile_kernels_bits(B, H, N, d, dtype):
+    # N(0,1) inputs, no row of which has a key 8 (log2) above the maximum of its first 64: no reference moves, and both kernels
+    # sum in one order
+    print(f"stage against tile kernel B={B} H={H} N={N} d={d} {dtype}", flush=True)
+    bits = _make(B, H, N, N, d, dtype, 49000 + N + d)
+    o, lse = run_gpu(*bits, dtype, d ** -0.5, bits=True)
+    o2, lse2 = run_gpu(*bits, dtype, d ** -0.5, variant=fa2.FA2_VARIANT_NARROW, bits=True)
+    assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
 
 
 # B, H, Nq, Nk, d, dtype, causal: 12 tiles and more of keys that drive the reference point (test_stage_plan_cpu.py: all staged).  bf16

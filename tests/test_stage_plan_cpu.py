@@ -5,7 +5,7 @@ import subprocess
 import pytest
 
 from paper_2312_11918_amd import build
-from test_gpu_stage import CASES, CASES_256, SINKING
+from test_gpu_stage import CASES, CASES_256, COMPANY, SAME_BITS, SINKING
 
 PROGRAM = r"""
 #include <stdio.h>
@@ -35,8 +35,9 @@ def taken(tmp_path_factory):
 
 def test_the_parity_cases_are_taken(taken):
     assert all(taken([(B, H, Nq, Nk, 256, causal) for B, H, Nq, Nk, _, causal, _ in CASES_256]))
-    assert all(taken([(B, H, Nq, Nk, 64, causal) for B, H, Nq, Nk, _, causal, _ in CASES] + [(26, 16, 256, n, 64, 0) for n in (128, 200, 256)]))
+    assert all(taken([(B, H, Nq, Nk, 64, causal) for B, H, Nq, Nk, _, causal, _ in CASES] + [(26, 16, 256, n, 64, 0) for n in (128, 256)]))
     assert all(taken([(B, H, Nq, Nk, d, causal) for B, H, Nq, Nk, d, _, causal in SINKING]))
+    assert all(taken([(*sizes, d, 0) for d, sizes in COMPANY.items()] + [(B, H, N, N, d, 0) for B, H, N, d, _ in SAME_BITS]))
 
 
 # measured with both launches, one clearly ahead
