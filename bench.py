@@ -41,14 +41,14 @@ SOFTMAX_VALU_SLOTS_PER_ELEMENT = 4.5
 PROFILED_TRAFFIC = {
     "B8_H16_N2048_d128_fp16": {"bytes": 270025349, "algorithmic_bytes": 269484032,
                                "profile": "profiles/fa2_fwd_fp16_d128_B8_H16_N2048.txt"},
-    "B32_H16_N512_d64_fp16": {"bytes": 135441756, "algorithmic_bytes": 135266304,
-                              "profile": "profiles/fa2_fwd_fp16_d64_B32_H16_N512.txt"},
+    "B32_H16_N512_d64_fp16": {"bytes": 135542251, "algorithmic_bytes": 135266304,
+                              "profile": "profiles/fa2_stage_fp16_d64_B32_H16_N512.txt"},
     "B2_H16_N8192_d128_bf16": {"bytes": 270027304, "algorithmic_bytes": 269484032,
                                "profile": "profiles/fa2_fwd_bf16_d128_B2_H16_N8192.txt"},
-    # one head's K and V (4 MiB) equal an XCD's L2 and the 64 query tiles of a head do not all run at once: K/V are
-    # fetched about twice per head.  386.5 MiB per 2.3 ms launch is 2 % of the HBM bandwidth.
-    "B1_H32_N16384_d64_fp16_koutliers": {"bytes": 405250232, "algorithmic_bytes": 270532608,
-                                         "profile": "profiles/fa2_fwd_fp16_d64_B1_H32_N16384_koutliers.txt"},
+    # one head's K and V (4 MiB) equal an XCD's L2, which its 64 query tiles, at different keys by and by, share: K/V are
+    # fetched about twice per head.  376.6 MiB per 2.1 ms launch is 2 % of the HBM bandwidth.
+    "B1_H32_N16384_d64_fp16_koutliers": {"bytes": 394935381, "algorithmic_bytes": 270532608,
+                                         "profile": "profiles/fa2_stage_fp16_d64_B1_H32_N16384_koutliers.txt"},
 }
 
 
@@ -361,7 +361,9 @@ def main():
                      "traffic": None if prof is None else prof["bytes"],
                      "traffic_source": None if prof is None else prof["profile"],
                      "algorithmic_flops_per_launch": flops, "algorithmic_hbm_bytes_per_launch": alg_bytes,
-                     "kernel": "fa2_fwd_kernel", "kernel_ms": round(ms, 5),
+                     # as the profile names it (none: not profiled)
+                     "kernel": None if prof is None else "_".join(os.path.basename(prof["profile"]).split("_")[:2]) + "_kernel",
+                     "kernel_ms": round(ms, 5),
                      "kernel_ms_is": "HIP events on the launch stream around back-to-back launches, per launch "
                                      "(one step = one launch of this kernel)",
                      "secondary": {k: roofs[k] for k in ("alu_roof_tflops", "frac_alu_roof", "hbm_floor_ms",

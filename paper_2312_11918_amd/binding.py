@@ -87,7 +87,8 @@ def _load_forward():
 
         try:
             loader = importlib.machinery.ExtensionFileLoader("_fa2_torch", _TORCH_PATH)
-            module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_fa2_torch", _TORCH_PATH, loader=loader))
+            spec = importlib.util.spec_from_file_location("_fa2_torch", _TORCH_PATH, loader=loader)
+            module = importlib.util.module_from_spec(spec)
             loader.exec_module(module)
             if module.torch_version != torch.__version__:
                 raise ImportError(f"built for torch {module.torch_version}, this is {torch.__version__}")

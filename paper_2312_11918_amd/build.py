@@ -38,8 +38,8 @@ def _hipcc(sources, library, verbose):
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` and the call on torch tensors, which uses the former, into
-    ``_fa2_torch.so``, next to this file; returns the former's path."""
+    """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` and the call on torch tensors, which uses the
+    former, into ``_fa2_torch.so``, next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
     _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES], LIBRARY, verbose)
     _build_torch_call(verbose)

@@ -73,7 +73,8 @@ int choose_variant(int B, int H, int Nq, int Nk, int d, int mask) {
   // Measured on MI355X with N(0,1) inputs: when its Q tiles fill whole rounds of the chip's 256 CUs (one workgroup
   // per CU, which then takes one Q tile of every round), the 8-wavefront, 256-row shape is faster than the
   // 4-wavefront, 128-row shape by 3-6 % at d = 128 at every N, and by 1-2 % at d = 64 from N = 4096 on (at d = 64
-  // below N = 2048 its two wavefronts per SIMD against three lose 2-5 %).  With many rounds that are not whole it
+  // below N = 2048 its two wavefronts per SIMD against three lose 2-5 %; what stage_accepts() leaves of d = 64 has one
+  // round of it, so that it chains there in an explicit choice only).  With many rounds that are not whole it
   // still gains at d = 128 from N = 2048 on; with few, the 128-row shape, two workgroups per CU, spreads the
   // remainder better.  d = 256 and partial tiles exist in the 128-row shape only.
   // Under the causal mask (one workgroup per pair of Q tiles, no chaining) it gains 1-3 % at d = 128 from N = 2048 on.

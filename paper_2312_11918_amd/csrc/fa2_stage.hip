@@ -1,34 +1,34 @@
 // Attention with the softmax mixed into the MFMAs: d = 64 with 64 query rows per wavefront, and d = 256.
 //
 // At d = 64 the softmax costs a SIMD more issue cycles than the matrix products: per 64 x 64 tile of S and wavefront 224
-// vector instructions (1296 cycles, the exponentials at half rate) against 32 MFMAs (1024 cycles).  Two things kept the tile
-// kernel of fa2_tile_kernel.h from either bound.  Its two or three wavefronts per SIMD run whole phases, softmax or MFMAs, and
-// a wavefront alone in its softmax issues only one vector instruction per 5.3 cycles (one exponential per 9.3), fewer under
-// another's MFMAs; and it reads one 1 KiB fragment from LDS per MFMA, which at full rate is all that the LDS delivers.
-// Here
+// vector instructions (1152 cycles, 64 of them exponentials at half rate) beside 32 MFMAs (1024 cycles of the matrix core, 128
+// of issue).  Two things kept the tile kernel of fa2_tile_kernel.h from either bound.  Its two or three wavefronts per SIMD run
+// whole phases, softmax or MFMAs, which overlap only as it happens; and it reads one 1 KiB fragment from LDS per MFMA.  Here
 //  * a wavefront owns two groups of 32 query rows, so that a K or V fragment read from LDS feeds two MFMAs, and a K/V tile
 //    staged by a workgroup of four wavefronts serves 256 rows;
 //  * the work is a pipeline of stages of 32 keys: stage s runs the softmax of S(s), GEMM-I of S(s+1) and GEMM-II with
-//    P~(s-1), and one MFMA alternates with the vector instructions of two elements per lane.  (One MFMA and two elements
-//    take 42 cycles per wavefront when two wavefronts share a SIMD, 45 alone.)
-// 212...221 registers, two wavefronts per SIMD, two workgroups per CU.  Bound by vector issue: 84 % of the cycles of the
-// resident wavefronts (75 % of all), at 1.75 GHz on N(0,1) inputs.  The bits are those of the tile kernel (but where the
-// reference point of a row moves after its first tile).  us before and after, in turn in one process: B1 H32 N16384
+//    P~(s-1), and one MFMA alternates with the vector instructions of two elements per lane.
+// 212...221 registers, two wavefronts per SIMD, two workgroups per CU.  Bound by vector issue where the loop is long: counted at
+// B1 H32 N16384, a tile takes its SIMD 1963 cycles, 1448 of them vector issue (261 instructions and the MFMAs): 74 % of all, 82 %
+// of those with both wavefronts there, at 1.74 GHz on N(0,1) inputs.  At B32 H16 N512 it is 45 % and 68 %: starts and ends around
+// 16 stages, 1.34 wavefronts per SIMD on average.  The bits are those of the tile kernel (but where the reference point of a
+// row moves, which both find out at different keys).  us before and after, in turn in one process: B1 H32 N16384
 // 2234 / 2055, B8 H32 N2048 304 / 278, B16 H32 N1024 166 / 156, B32 H16 N512 50.1 / 48.6, B8 H16 N2047 154 / 148, causal B1 H32
 // N16384 1160 / 1054, B8 H32 N2048 182 / 175.
 //
-// At d = 256 O^T alone takes half of the 512 registers that the only wavefront of a SIMD has, so a wavefront owns one group of 32
-// rows, and a stage is GEMM-I of S(s+1), then GEMM-II with P~(s-1), one element of the softmax of S(s) after every second MFMA.  The
-// tile kernel's wavefront has nobody to overlap its softmax with.  An MFMA, 32 cycles, takes about 68 (34 ns at 2.0 GHz); the LDS is
-// busy for 43 of them, with one fragment per MFMA of four wavefronts and the refills.  What the rest goes to is not known.  us before and after: B4 H8 N4095 603 / 561,
-// B6 H12 N1000 122 / 111, B11 H8 N777 104 / 92, B2 H16 N1024 41.0 / 39.2, B9 H24 Nq3 Nk355 20.6 / 18.8; causal B4 H32 N1116 157 / 134,
-// B9 H8 N2709 420 / 344.  It makes no difference there: 6, 12 or 16 fragments in flight instead of 8 (0...-2 %), the two products
-// mixed (0...-1 %), the refills spread over a stage (-1...+1 %).  d = 128 in this form (two groups, one wavefront per SIMD): 6...16 %
-// slower than the tile kernel, which has two.
+// At d = 256 O^T alone takes half of the 512 registers that the only wavefront of a SIMD has, so a wavefront owns one group of
+// 32 rows, and a stage is GEMM-I of S(s+1), then GEMM-II with P~(s-1), one element of the softmax of S(s) after every second
+// MFMA.  The tile kernel's wavefront has nobody to overlap its softmax with.  An MFMA, 32 cycles, takes 71 of its SIMD (34 ns
+// settled, at 2.0 GHz); the wavefront issues in 51 % of its cycles, waits for its turn in 24 % and for a counter or
+// a barrier in 26 % (counted at B4 H8 N4095).  us before and after: B4 H8 N4095 603 / 561, B6 H12 N1000 122 / 111, B11 H8 N777
+// 104 / 92, B2 H16 N1024 41.0 / 39.2, B9 H24 Nq3 Nk355 20.6 / 18.8; causal B4 H32 N1116 157 / 134, B9 H8 N2709 420 / 344.  It
+// makes no difference there: 6, 12 or 16 fragments in flight instead of 8 (0...-2 %), the two products mixed (0...-1 %), the
+// refills spread over a stage (-1...+1 %).  d = 128 in this form (two groups, one wavefront per SIMD): 6...16 % slower than the
+// tile kernel, which has two.
 //
-// Tried and not kept at d = 64: eight wavefronts (512 rows) per workgroup, level at N = 16384, 4...8 % slower below; two wavefronts (128
-// rows), 6...11 % slower (the K/V refill doubles); one group of rows and three wavefronts per SIMD, 4...9 % slower; four
-// K/V buffers instead of two, 0...-4 %; alternating priorities of the two workgroups of a CU, 0...-1 %.
+// Tried and not kept at d = 64: eight wavefronts (512 rows) per workgroup, level at N = 16384, 4...8 % slower below; two
+// wavefronts (128 rows), 6...11 % slower (the K/V refill doubles); one group of rows and three wavefronts per SIMD, 4...9 %
+// slower; four K/V buffers instead of two, 0...-4 %; alternating priorities of the two workgroups of a CU, 0...-1 %.
 #include "fa2_stage_plan.h"
 #include "fa2_tile_kernel.h"
 
@@ -47,10 +47,9 @@ template <int N> using Int = std::integral_constant<int, N>;
 // kCausal: one Q tile per workgroup, the longest first.  kRagged: any Nq and Nk, as in fa2_fwd_kernel, but the count of K/V
 // tiles is not padded: a wavefront runs the tiles that its own rows see and only keeps the boundaries of the others.
 template <int DT, int kD, bool kCausal, bool kRagged>
-__global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                                                                  const uint16_t* __restrict__ V, uint16_t* __restrict__ O,
-                                                                  float* __restrict__ LSE, int H, int Nq, int Nk,
-                                                                  float scale_log2e, int n_qtiles, int total) {
+__global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, uint16_t* __restrict__ O,
+    float* __restrict__ LSE, int H, int Nq, int Nk, float scale_log2e, int n_qtiles, int total) {
   using E = Elem<DT>;
   using T = Tile<kD>;
   constexpr int kGroups = groups_of(kD);
@@ -85,8 +84,8 @@ __global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kerne
       bh = tile / n_qtiles;
       qt = tile - bh * n_qtiles;
     } else if (heads % kXcds == 0) {
-      // Heads stay on one XCD, in groups of two rounds of its 64 workgroups (at least four heads): within a group
-      // the longest Q tiles of all heads start first, so that the short ones fill the end, and a group's K and V stay in the L2
+      // Heads stay on one XCD, in groups of 128 workgroups, two rounds of its CUs at d = 64 and four at d = 256 (at least four
+      // heads): within a group the longest Q tiles of all heads start first, so that the short ones fill the end, and a group's K and V stay in the L2
       // (all heads as one group: 1...5 % slower at N = 1024...4096).
       const int mine = heads / kXcds;
       const int groups = max(1, mine / max(4, (128 + n_qtiles - 1) / n_qtiles));
@@ -180,8 +179,8 @@ __global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kerne
       for (int v = 0; v < 16; ++v)
         if (8 * (v / 4) + (v % 4) > visible + (kCausal ? 32 * g : 0)) s[g][v] = -INFINITY;
   };
-  // Element v of S for the softmax.  At d = 256 S is in accumulation registers and is read where it is needed (the compiler reads
-  // all of it at the start of a stage).  It does not see that this reads what MFMAs wrote: 16 others stand between.
+  // Element v of S for the softmax.  At d = 256 S is in accumulation registers and is read where it is needed (the compiler
+  // reads all of it at the start of a stage).  It does not see that this reads what MFMAs wrote: 16 others stand between.
   auto logit = [&](const f32x16& s, int v) __attribute__((always_inline)) {
     if constexpr (kD == 64) {
       return s[v];
@@ -208,8 +207,8 @@ __global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kerne
     return fmaxf(max_with_partner_half_raw(mx) * scale_log2e, kLowest);
   };
 
-  // One stage (parity x), two groups: GEMM-II with pf[1 - x] and the V half tile `vt`, mixed with the softmax of st[x][0] -> pf[x][0], then
-  // GEMM-I of the K half tile `kt` -> st[1 - x], mixed with the softmax of st[x][1].  In this order S of group 0 is dead
+  // One stage (parity x), two groups: GEMM-II with pf[1 - x] and the V half tile `vt`, mixed with the softmax of st[x][0] ->
+  // pf[x][0], then GEMM-I of the K half tile `kt` -> st[1 - x], mixed with the softmax of st[x][1].  In this order S of group 0 is dead
   // when GEMM-I writes its successor (all at once would take 40 registers too many), and that successor, which the next
   // stage needs first, is done four MFMAs before this stage ends.  The first stage has neither product, the last no GEMM-I.
   auto stage = [&](auto x_tag, auto gemm1_tag, auto gemm2_tag, const uint16_t* kt, const uint16_t* vt)
@@ -228,8 +227,8 @@ __global__ __launch_bounds__(kWaves * 64, kD == 64 ? 2 : 1) void fa2_stage_kerne
 #pragma unroll
     for (int f = 0; f < (kFrags < kRing ? kFrags : kRing); ++f) ring[f] = frag(f);
 
-    // The softmax of one group, a pair of elements after each of the 8 MFMAs that `mfma` issues (one group: over four): the exponents of the next
-    // pair, the exponentials of this one, sum and P~ of the last one.  Each part is pinned where it stands; left free, the
+    // The softmax of one group, a pair of elements after each of the 8 MFMAs that `mfma` issues (one group: over four): the
+    // exponents of the next pair, the exponentials of this one, sum and P~ of the last one.  Each part is pinned where it stands; left free, the
     // compiler moves all of it behind the MFMAs, to the first use of P~.
     auto softmax = [&](auto g_tag, auto mfma) __attribute__((always_inline)) {
       constexpr int g = decltype(g_tag)::value;

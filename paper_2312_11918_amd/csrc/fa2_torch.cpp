@@ -5,8 +5,8 @@
 // attribute reads the rest.
 //
 // forward() takes plain strided tensors of the current device and does nothing but what the Python path does with them; for
-// everything else (another device, a subclass, a tensor that a transform has wrapped, an active torch function or dispatch mode, a
-// capture that needs scratch memory, arguments that are refused) it returns None before it has allocated or launched
+// everything else (another device, a subclass, a tensor that a transform has wrapped, an active torch function or dispatch
+// mode, a capture that needs scratch memory, arguments that are refused) it returns None before it has allocated or launched
 // anything, and the Python path goes on, with its own checks and errors.
 #include <torch/csrc/python_headers.h>
 
