@@ -22,11 +22,16 @@ namespace fa2 {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kNoKey = -3.402823466e38f;   // reference point of a part that has seen no key: the lowest finite number
 constexpr int kMaxWaves = 8;   // wavefronts per workgroup
+constexpr int kFewSplits = 16;       // most splits that the merge adds up with one thread per column
+constexpr int kMergeThreads = 256;   // threads of a workgroup of the merge, with more splits
 constexpr int kUnroll = 4;     // keys per lane group and step (8: 1...7 % slower, 2: 0...5 % slower)
 
 // element i of eight 16-bit elements as fp32
@@ -213,28 +218,88 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fa2_decode_kernel(
   }
 }
 
-// Merge of the splits of one (b, h): thread t is column t.  Latency-bound (a few KiB per workgroup), so the loads of
-// the loop are independent of each other.
+// Merge of the splits of one (b, h).  Latency-bound (a few KiB per head).
+//  * Up to kFewSplits: thread t is column t, and the loads of a loop over the splits are independent of each other.
+//  * More: 16 columns per wavefront, lane t the columns 4 (t % 4) ... + 3 of the splits t / 4, t / 4 + 16, ..., which it merges
+//    four at a time, all their loads under way at once; the sixteen lanes of a column are merged at the end.  Up to 16 splits
+//    this is the slower one (8 / 10 / 16 splits, d = 64 / 128 / 128: 28.0 / 12.05 / 9.82 us a call, 27.2 / 11.75 / 9.44 by columns).
+// Per call, by columns / by lane groups: B1 H2 Nk32768 d128 (128 splits) 18.9 / 11.6 us, B1 H6 Nk3000 d256 (42) 11.8 / 9.2, B1 H6
+// Nk32768 d64 (42) 16.4 / 14.1, B3 H2 Nk20000 d256 (42) 27.9 / 25.2, B1 H12 Nk3000 d128 (21) 10.3 / 9.2.
 template <int DT, int D>
-__global__ __launch_bounds__(D) void fa2_decode_merge_kernel(const float* __restrict__ part_o,
-                                                             const float* __restrict__ part_ml,
-                                                             uint16_t* __restrict__ O, float* __restrict__ LSE,
-                                                             int splits) {
-  const size_t bh = blockIdx.x;
-  const float* po = part_o + bh * splits * D + threadIdx.x;
-  const float* ml = part_ml + 2 * bh * splits;
-  float m = -INFINITY;
+__global__ __launch_bounds__(kMergeThreads) void fa2_decode_merge_kernel(const float* __restrict__ part_o,
+                                                                         const float* __restrict__ part_ml,
+                                                                         uint16_t* __restrict__ O, float* __restrict__ LSE,
+                                                                         int splits) {
+  constexpr int kWavesPerHead = D / 16, kAhead = 4;
+  if (splits <= kFewSplits) {
+    const size_t bh = blockIdx.x;
+    const float* ml = part_ml + 2 * bh * splits;
+    const float* po = part_o + bh * splits * D + threadIdx.x;
+    float m = -INFINITY;
 #pragma unroll 8
-  for (int s = 0; s < splits; ++s) m = fmaxf(m, ml[2 * s]);
-  float l = 0.f, sum = 0.f;
+    for (int s = 0; s < splits; ++s) m = fmaxf(m, ml[2 * s]);
+    float l = 0.f, sum = 0.f;
 #pragma unroll 8
-  for (int s = 0; s < splits; ++s) {
-    const float w = __builtin_amdgcn_exp2f(ml[2 * s] - m);   // reference points are finite (kNoKey at least)
-    l += w * ml[2 * s + 1];
-    sum += w * po[(size_t)s * D];
+    for (int s = 0; s < splits; ++s) {
+      const float w = __builtin_amdgcn_exp2f(ml[2 * s] - m);   // reference points are finite (kNoKey at least)
+      l += w * ml[2 * s + 1];
+      sum += w * po[(size_t)s * D];
+    }
+    O[bh * D + threadIdx.x] = round16<DT>(sum / l);
+    if (LSE != nullptr && threadIdx.x == 0) LSE[bh] = m * kLn2 + __builtin_logf(l);
+    return;
   }
-  O[bh * D + threadIdx.x] = round16<DT>(sum / l);
-  if (LSE != nullptr && threadIdx.x == 0) LSE[bh] = m * kLn2 + __builtin_logf(l);
+  const int lane = threadIdx.x & 63, group = lane >> 2;
+  const unsigned wave = blockIdx.x * (kMergeThreads / 64) + (threadIdx.x >> 6);
+  const size_t bh = wave / kWavesPerHead;
+  const int column = 16 * (wave % kWavesPerHead) + 4 * (lane & 3);
+  const float* po = part_o + bh * splits * D + column;
+  const f32x2* ml = reinterpret_cast<const f32x2*>(part_ml) + bh * splits;
+  float m = kNoKey, l = 0.f;   // reference points are finite (kNoKey at least)
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s = group; s < splits; s += 16 * kAhead) {
+    f32x2 y[kAhead];
+    f32x4 x[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int at = min(s + 16 * i, splits - 1);
+      y[i] = ml[at];
+      x[i] = *reinterpret_cast<const f32x4*>(po + (size_t)at * D);
+    }
+    float m_new = m;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) m_new = fmaxf(m_new, y[i][0]);
+    const float alpha = weight(m, m_new);
+    m = m_new;
+    l *= alpha;
+    o *= alpha;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const float w = s + 16 * i < splits ? weight(y[i][0], m) : 0.f;
+      l = __builtin_fmaf(w, y[i][1], l);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[c] = __builtin_fmaf(w, x[i][c], o[c]);
+    }
+  }
+  float m_all = m;
+#pragma unroll
+  for (int i = 4; i < 64; i *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, i));
+  const float w = weight(m, m_all);
+  l *= w;
+  o *= w;
+#pragma unroll
+  for (int i = 4; i < 64; i *= 2) {
+    l += __shfl_xor(l, i);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) o[c] += __shfl_xor(o[c], i);
+  }
+  if (group == 0) {
+    uint16_t* out = O + bh * D + column;
+    const uint32_t lo = round16<DT>(o[0] / l) | (uint32_t)round16<DT>(o[1] / l) << 16;
+    const uint32_t hi = round16<DT>(o[2] / l) | (uint32_t)round16<DT>(o[3] / l) << 16;
+    *reinterpret_cast<u32x2*>(out) = u32x2{lo, hi};
+    if (LSE != nullptr && column == 0) LSE[bh] = m_all * kLn2 + __builtin_logf(l);
+  }
 }
 
 struct Plan {
@@ -291,7 +356,9 @@ template <int DT, int D> int launch(const Problem& p, void* workspace, size_t wo
   const int rc = enqueue(fa2_decode_kernel<DT, D, true>, heads * plan.splits, plan.waves * 64, p.stream, q, k, v, o, p.LSE,
                          part_o, part_ml, p.H, p.Nk, p.scale_log2e, plan.splits, plan.chunk);
   if (rc != FA2_OK) return rc;
-  return enqueue(fa2_decode_merge_kernel<DT, D>, heads, D, p.stream, part_o, part_ml, o, p.LSE, plan.splits);
+  const bool few = plan.splits <= kFewSplits;
+  return enqueue(fa2_decode_merge_kernel<DT, D>, few ? heads : heads * (D / 16) / (kMergeThreads / 64), few ? D : kMergeThreads,
+                 p.stream, part_o, part_ml, o, p.LSE, plan.splits);
 }
 
 }  // namespace

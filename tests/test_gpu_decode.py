@@ -118,3 +118,24 @@ def test_single_query_keys_masked_by_the_lowest_value(Nk, live, d, dtype, split)
     half_ulp = 2.0 ** (-11 if dtype == "fp16" else -8)
     assert np.all(np.abs(o - o_ref) <= np.abs(o_ref) * half_ulp + 1e-5)
     assert np.all(np.abs(lse - lse_ref) <= 1e-5 * np.maximum(1.0, np.abs(lse_ref)))
+
+
+@pytest.mark.parametrize("Nk,d,dtype", [
+    (4096, 64, "fp16"),     # 16 splits of a step per wavefront: the last count merged by one thread per column
+    (4352, 64, "bf16"),     # 17: the first merged by lane groups
+    (8192, 128, "bf16"),    # 64: every lane group holds four
+    (8320, 128, "fp16"),    # 65: one of them a fifth
+    (16384, 256, "bf16"),   # 256, the most of one head: four rounds of four
+])
+def test_single_query_merge_of_many_splits(Nk, d, dtype):
+    print(f"decode merge Nk={Nk} d={d} {dtype}", flush=True)
+    torch_gpu()
+    splits = fa2.fa2_workspace_bytes(1, 1, 1, Nk, d) // (4 * (d + 2))
+    assert splits == Nk * d // (8 * 4 * 512)
+    qb, kb, vb = _make(1, 1, 1, Nk, d, dtype, 8100 + Nk + d, 0.02)
+    scale = float(np.float32(d) ** np.float32(-0.5))
+    o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale)
+    o, lse = _decode(qb, kb, vb, dtype, scale, True)
+    half_ulp = 2.0 ** (-11 if dtype == "fp16" else -8)
+    assert np.all(np.abs(o - o_ref) <= np.abs(o_ref) * half_ulp + 1e-5)
+    assert np.all(np.abs(lse - lse_ref) <= 1e-5 * np.maximum(1.0, np.abs(lse_ref)))
