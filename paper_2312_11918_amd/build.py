@@ -11,6 +11,7 @@ SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile 
 SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query per sequence, keys split
                  os.path.join(_PKG, "csrc", "fa2_split.hip")]        # few query tiles, keys split
 STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64 and 256, softmax mixed into the MFMAs
+SHORT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_short.hip")]        # few query rows in all
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
 TORCH_SOURCE = os.path.join(_PKG, "csrc", "fa2_torch.cpp")           # the Python call on torch tensors
@@ -41,7 +42,7 @@ def build_library(verbose: bool = False) -> str:
     """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` and the call on torch tensors, which uses the
     former, into ``_fa2_torch.so``, next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
-    _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES], LIBRARY, verbose)
+    _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES], LIBRARY, verbose)
     _build_torch_call(verbose)
     return LIBRARY
 
@@ -107,8 +108,12 @@ def resource_usage(sources=SOURCES):
             continue
         m = re.search(r"fa2_stage_kernelILi(\d+)ELi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
         if m:
-            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}{', causal' if m[3] == '1' else ''}"
+            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}, {m[3]} wavefronts{', causal' if m[4] == '1' else ''}"
                          f"{', partial tiles' if m[4] == '1' else ''}>")
+            continue
+        m = re.search(r"fa2_short_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", k["mangled"])
+        if m:
+            k["name"] = f"fa2_short_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}, {m[3]} wavefronts{', causal' if m[4] == '1' else ''}>"
             continue
         m = re.search(r"(fa2_(?:decode|decode_merge|split_merge)_kernel)ILi(\d+)ELi(\d+)E(?:Lb(\d)E)?", k["mangled"])
         if m:
@@ -123,7 +128,7 @@ if __name__ == "__main__":
     import sys
 
     if "--resource-usage" in sys.argv:
-        rows = resource_usage([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES])
+        rows = resource_usage([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES])
         print("| kernel | VGPRs | AGPRs | SGPRs | scratch B/lane | LDS B/workgroup | wavefronts/SIMD |")
         print("|---|---|---|---|---|---|---|")
         for k in sorted(rows, key=lambda r: r["name"]):

@@ -1,4 +1,5 @@
 // FlashAttention-2 forward pass for gfx950: choice of the tile shape, launches and C ABI of libfa2.
+#include "fa2_short_plan.h"
 #include "fa2_tile_kernel.h"
 
 namespace {
@@ -107,6 +108,12 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
                          static_cast<hipStream_t>(stream)};
     if (fa2::decode_accepts(B, H, Nq)) return fa2::decode(p, workspace, workspace_bytes);
     int rc;
+    int waves = fa2::short_waves(B, H, Nq, Nk, d, p.causal, false);
+    if (waves != 0 && workspace != nullptr && fa2::short_waves(B, H, Nq, Nk, d, p.causal, true) == 0) {
+      const size_t slices = fa2::split_workspace(B, H, Nq, Nk, d, p.causal);
+      if (slices != 0 && workspace_bytes >= slices) waves = 0;
+    }
+    if (waves != 0) return fa2::short_tiles(p, waves);
     if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc)) return rc;
     variant = choose_variant(B, H, Nq, Nk, d, mask);
   }
@@ -157,7 +164,8 @@ extern "C" size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int m
   if (B <= 0 || H <= 0 || Nq <= 0 || Nk <= 0 || (mask != FA2_MASK_NONE && mask != FA2_MASK_CAUSAL)) return 0;
   if (!sizes_fit(B, H, Nq, Nk, d, mask)) return 0;
   if (fa2::decode_accepts(B, H, Nq)) return fa2::decode_workspace(B, H, Nk, d);
-  return fa2::split_workspace(B, H, Nq, Nk, d, mask == FA2_MASK_CAUSAL);
+  const bool causal = mask == FA2_MASK_CAUSAL;
+  return fa2::short_waves(B, H, Nq, Nk, d, causal, true) != 0 ? 0 : fa2::split_workspace(B, H, Nq, Nk, d, causal);
 }
 
 extern "C" int fa2_tile_shape(int B, int H, int Nq, int Nk, int d, int mask) {
