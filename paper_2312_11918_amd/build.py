@@ -115,6 +115,10 @@ def resource_usage(sources=SOURCES):
         if m:
             k["name"] = f"fa2_short_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}, {m[3]} wavefronts{', causal' if m[4] == '1' else ''}>"
             continue
+        m = re.search(r"fa2_short_merge_kernelILi(\d+)ELi(\d+)ELb(\d)E", k["mangled"])
+        if m:
+            k["name"] = f"fa2_short_merge_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}{', causal' if m[3] == '1' else ''}>"
+            continue
         m = re.search(r"(fa2_(?:decode|decode_merge|split_merge)_kernel)ILi(\d+)ELi(\d+)E(?:Lb(\d)E)?", k["mangled"])
         if m:
             flag = {None: "", "0": ""}.get(m[4], ", causal" if "split" in m[1] else ", keys split")

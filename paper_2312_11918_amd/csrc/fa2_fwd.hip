@@ -1,5 +1,4 @@
 // FlashAttention-2 forward pass for gfx950: choice of the tile shape, launches and C ABI of libfa2.
-#include "fa2_short_plan.h"
 #include "fa2_tile_kernel.h"
 
 namespace {
@@ -108,12 +107,10 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
                          static_cast<hipStream_t>(stream)};
     if (fa2::decode_accepts(B, H, Nq)) return fa2::decode(p, workspace, workspace_bytes);
     int rc;
-    int waves = fa2::short_waves(B, H, Nq, Nk, d, p.causal, false);
-    if (waves != 0 && workspace != nullptr && fa2::short_waves(B, H, Nq, Nk, d, p.causal, true) == 0) {
-      const size_t slices = fa2::split_workspace(B, H, Nq, Nk, d, p.causal);
-      if (slices != 0 && workspace_bytes >= slices) waves = 0;
-    }
-    if (waves != 0) return fa2::short_tiles(p, waves);
+    fa2::ShortPlan plan = fa2::short_plan(B, H, Nq, Nk, d, p.causal, workspace != nullptr);
+    if (plan.slices > 1 && workspace_bytes < fa2::short_workspace(B, H, Nq, d, plan))
+      plan = fa2::short_plan(B, H, Nq, Nk, d, p.causal, false);
+    if (plan.waves != 0) return fa2::short_tiles(p, plan, workspace);
     if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc)) return rc;
     variant = choose_variant(B, H, Nq, Nk, d, mask);
   }
@@ -165,7 +162,8 @@ extern "C" size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int m
   if (!sizes_fit(B, H, Nq, Nk, d, mask)) return 0;
   if (fa2::decode_accepts(B, H, Nq)) return fa2::decode_workspace(B, H, Nk, d);
   const bool causal = mask == FA2_MASK_CAUSAL;
-  return fa2::short_waves(B, H, Nq, Nk, d, causal, true) != 0 ? 0 : fa2::split_workspace(B, H, Nq, Nk, d, causal);
+  const fa2::ShortPlan plan = fa2::short_plan(B, H, Nq, Nk, d, causal, true);
+  return plan.waves != 0 ? fa2::short_workspace(B, H, Nq, d, plan) : fa2::split_workspace(B, H, Nq, Nk, d, causal);
 }
 
 extern "C" int fa2_tile_shape(int B, int H, int Nq, int Nk, int d, int mask) {

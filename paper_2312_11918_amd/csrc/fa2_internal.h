@@ -8,6 +8,7 @@
 #include <tuple>
 
 #include "fa2.h"
+#include "fa2_short_plan.h"
 #include "fa2_split_plan.h"
 
 namespace fa2 {
@@ -46,8 +47,10 @@ __attribute__((visibility("hidden"))) int decode(const Problem& p, void* workspa
 __attribute__((visibility("hidden"))) size_t split_workspace(int B, int H, int Nq, int Nk, int d, bool causal);
 __attribute__((visibility("hidden"))) bool split_tiles(const Problem& p, void* workspace, size_t workspace_bytes, int* rc);
 
-// fa2_short.hip: few query rows in all, for the problems that short_waves() takes; returns the launch's return code.
-__attribute__((visibility("hidden"))) int short_tiles(const Problem& p, int waves);
+// fa2_short.hip: few query rows in all, as short_plan() says; returns the launch's return code.  short_workspace(): the bytes that
+// the slices of a plan take.
+__attribute__((visibility("hidden"))) size_t short_workspace(int B, int H, int Nq, int d, const ShortPlan& plan);
+__attribute__((visibility("hidden"))) int short_tiles(const Problem& p, const ShortPlan& plan, void* workspace);
 
 // fa2_stage.hip: d = 64 with 64 query rows per wavefront, and d = 256.  Launches nothing and is false where the tile kernel's
 // whole launch is the better one; otherwise *rc is the launch's return code.

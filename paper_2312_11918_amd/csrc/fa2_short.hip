@@ -13,6 +13,10 @@
 // causal d = 64, 128, 256 10.4 / 4.6, 14.4 / 6.3, 24.0 / 10.9; B1 H2 N1111 d64 13.8 / 7.6; B3 H8 N193 d256 14.7 / 11.4; B1 H2 Nq35
 // Nk534 d128 11.7 / 8.0.
 //
+// Few tiles of many keys: the keys are cut into slices over workgroups as well, where the caller gives a workspace, and a second
+// kernel merges their partial O (16 KiB per workgroup at d = 128, a quarter of what slices of 128-row tiles write): B1 H16 Nq32
+// Nk3000 d128 15.8 / 12.1, B1 H6 Nq26 Nk1334 d256 25.1 / 14.5, B1 H2 Nq128 Nk1024 d128 12.1 / 8.8.
+//
 // One buffer per wavefront for K and one for V: the next block of K is requested when this one's fragments have been read, under
 // both products and the softmax, the next of V when this one's have, under GEMM-II and the next GEMM-I.  110, 191 and 501 registers at
 // d = 64, 128, 256: four, two and one wavefront per SIMD, which is what LDS holds as well.
@@ -27,10 +31,20 @@ constexpr int kShortKeys = 32;   // keys per block: wavefront w takes blocks w, 
 // See fa2_fwd_kernel for the operands' layouts, the swizzles and the transposed products, which are the same, and for partial
 // tiles: rows past Nq - 1 are computed from a copy of the last row and not stored, keys past Nk - 1 masked copies of the last key.
 // kCausal: blocks past the diagonal are not visited, and only the tile's own block crosses it.
+// A workgroup takes a slice of cut.chunk blocks of its tile's keys (all of them where cut.slices is 1).  A tile whose keys lie in
+// several leaves its O^T unnormalised in cut.part_o, with the reference points and sums in cut.part_ml, for fa2_short_merge_kernel.
+struct ShortCut {
+  float* part_o = nullptr;    // [tile over all heads][slice][register quad][lane] of 4
+  float* part_ml = nullptr;   // [tile over all heads][slice][row][2]: reference point (scaled, log2), row sum
+  int chunk = 0x7fffffff;     // blocks per slice
+  int slices = 1;             // of the longest tile
+  int items = 0;              // workgroups per head
+};
+
 template <int DT, int kD, int kWv, bool kCausal>
 __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa2_short_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, uint16_t* __restrict__ O,
-    float* __restrict__ LSE, int H, int Nq, int Nk, float scale_log2e, int n_qtiles, int total) {
+    float* __restrict__ LSE, int H, int Nq, int Nk, float scale_log2e, int n_qtiles, int total, ShortCut cut) {
   using E = Elem<DT>;
   using T = Tile<kD>;
   constexpr int kKSteps = kD / 16;                  // MFMA steps along d of GEMM-I: fragments of K per block
@@ -51,18 +65,27 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, hh = lane >> 5;   // query, half of the wavefront
 
-  int bh, qt;
+  // The items of a head run slice by slice, so that neighbouring workgroups read the same keys; slice s concerns every tile, or
+  // under the mask those from its own first key on, the last tile first.
+  int bh, item;
   if constexpr (kCausal) {   // the longest of every head first
-    const int heads = total / n_qtiles, c = blockIdx.x / heads;
-    bh = blockIdx.x - c * heads;
-    qt = n_qtiles - 1 - c;
-  } else {   // a contiguous range of Q tiles per XCD: those of one head share an L2
+    const int heads = total / cut.items;
+    item = blockIdx.x / heads;
+    bh = blockIdx.x - item * heads;
+  } else {   // a contiguous range per XCD: those of one head share an L2
     const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
     const int per = total / kXcds, rem = total % kXcds;
-    const int tile = xcd * per + min(xcd, rem) + idx;
-    bh = tile / n_qtiles;
-    qt = tile - bh * n_qtiles;
+    const int at = xcd * per + min(xcd, rem) + idx;
+    bh = at / cut.items;
+    item = at - bh * cut.items;
   }
+  int slice = 0;
+  for (int n = n_qtiles; item >= n;) {
+    item -= n;
+    ++slice;
+    if constexpr (kCausal) n -= cut.chunk;   // (a tile is one block long)
+  }
+  const int qt = kCausal ? n_qtiles - 1 - item : item;
   const size_t row_stride = (size_t)H * kD;
   const size_t q_base = ((size_t)(bh / H) * Nq * H + (size_t)(bh % H)) * kD;
   const size_t kv_base = ((size_t)(bh / H) * Nk * H + (size_t)(bh % H)) * kD;
@@ -106,7 +129,9 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
     }
   }
 
-  const int n_blocks = kCausal ? min(qt + 1, (Nk + kShortKeys - 1) / kShortKeys) : (Nk + kShortKeys - 1) / kShortKeys;
+  const int all_blocks = kCausal ? min(qt + 1, (Nk + kShortKeys - 1) / kShortKeys) : (Nk + kShortKeys - 1) / kShortKeys;
+  const int first = slice * cut.chunk;   // (0 in the only slice)
+  const int n_blocks = min(all_blocks - first, cut.chunk);
   const int row = qt * kShortRows + r;
   u32x4 qf[kKSteps];
   {
@@ -116,8 +141,8 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wave < n_blocks) {
-    stage_in(true_type{}, wave);
-    stage_in(false_type{}, wave);
+    stage_in(true_type{}, first + wave);
+    stage_in(false_type{}, first + wave);
   }
   __builtin_amdgcn_sched_barrier(0);
 
@@ -132,8 +157,9 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
 
   constexpr int kWaitLast = (kLoads & 15) | ((kLoads >> 4) << 14) | 0x0F70;   // all but the kLoads last loads have landed
   constexpr int kWaitLoads = 0x0F70, kWaitLds = 0xC07F;                       // vmcnt(0), lgkmcnt(0)
-  for (int j = wave; j < n_blocks; j += kWv) {
-    const bool more = j + kWv < n_blocks;
+  const int end_block = first + n_blocks;
+  for (int j = first + wave; j < end_block; j += kWv) {
+    const bool more = j + kWv < end_block;
     // K of this block has landed (its V was requested after it)
     __builtin_amdgcn_s_waitcnt(kWaitLast);
     __builtin_amdgcn_sched_barrier(0);
@@ -234,7 +260,6 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
     w[i] = __builtin_amdgcn_exp2f(w[i] - m);
     if (i < parts) l = __builtin_fmaf(w[i], ml_lds[i * kShortRows + r][1], l);
   }
-  const float inv_l = 1.0f / l;
   constexpr int kMyQuads = kQuads / kWv;
   f32x4 sum[kMyQuads];
 #pragma unroll
@@ -250,6 +275,15 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
       for (int c = 0; c < 4; ++c) sum[n][c] = __builtin_fmaf(wi, y[c], sum[n][c]);
     }
   }
+  if (all_blocks > cut.chunk) {
+    const size_t slot = ((size_t)bh * n_qtiles + qt) * cut.slices + slice;
+    f32x4* const po = reinterpret_cast<f32x4*>(cut.part_o) + (slot * kQuads + wave * kMyQuads) * 64 + lane;
+#pragma unroll
+    for (int n = 0; n < kMyQuads; ++n) po[n * 64] = sum[n];
+    if (wave == 0 && hh == 0) reinterpret_cast<f32x2*>(cut.part_ml)[slot * kShortRows + r] = f32x2{m, l};
+    return;
+  }
+  const float inv_l = 1.0f / l;
   uint16_t* out = O + q_base + (size_t)row * row_stride;
   if constexpr (kMyQuads == 1) {
     const u32x2 x = {E::pack2(sum[0][0] * inv_l, sum[0][1] * inv_l), E::pack2(sum[0][2] * inv_l, sum[0][3] * inv_l)};
@@ -274,25 +308,90 @@ __global__ __launch_bounds__(kWv * 64, kD == 64 ? 4 : kD == 128 ? 2 : 1) void fa
     LSE[(size_t)bh * Nq + row] = m * 0.69314718055994530942f + __builtin_logf(l);
 }
 
-template <int DT, int kD, int kWv> int launch(const Problem& p) {
-  const int n_q = (p.Nq + kShortRows - 1) / kShortRows, total = p.B * p.H * n_q;
+// Merge of the slices of one tile: a wavefront holds one quad of columns, as the kernel above left it.
+template <int DT, int kD, bool kCausal>
+__global__ __launch_bounds__(256) void fa2_short_merge_kernel(ShortCut cut, uint16_t* __restrict__ O, float* __restrict__ LSE, int H,
+                                                              int Nq, int n_qtiles) {
+  using E = Elem<DT>;
+  constexpr int kQuads = kD / 8;
+  const int lane = threadIdx.x & 63, r = lane & 31, hh = lane >> 5;
+  const int quad = blockIdx.x % (kQuads / 4) * 4 + (threadIdx.x >> 6), tile = blockIdx.x / (kQuads / 4);
+  const int bh = tile / n_qtiles, qt = tile - bh * n_qtiles;
+  const int n = kCausal ? (qt + cut.chunk) / cut.chunk : cut.slices;   // slices that hold keys of this tile
+  const int row = qt * kShortRows + r;
+  if (n == 1 || row >= Nq) return;
+  const size_t slot = (size_t)tile * cut.slices;
+  const f32x4* po = reinterpret_cast<const f32x4*>(cut.part_o) + (slot * kQuads + quad) * 64 + lane;
+  const f32x2* ml = reinterpret_cast<const f32x2*>(cut.part_ml) + slot * kShortRows + r;
+  float m = kLowest, l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  constexpr int kAhead = 4;   // slices whose loads are under way at once
+  for (int s = 0; s < n; s += kAhead) {
+    f32x4 x[kAhead];
+    f32x2 y[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int at = min(s + i, n - 1);
+      x[i] = po[(size_t)at * kQuads * 64];
+      y[i] = ml[(size_t)at * kShortRows];
+    }
+    float m_new = m;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) m_new = fmaxf(m_new, y[i][0]);
+    const float alpha = __builtin_amdgcn_exp2f(m - m_new);   // reference points are finite (kLowest at least)
+    m = m_new;
+    l *= alpha;
+    o *= alpha;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const float w = s + i < n ? __builtin_amdgcn_exp2f(y[i][0] - m) : 0.f;
+      l = __builtin_fmaf(w, y[i][1], l);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[c] = __builtin_fmaf(w, x[i][c], o[c]);
+    }
+  }
+  const float inv_l = 1.0f / l;
+  const u32x2 out = {E::pack2(o[0] * inv_l, o[1] * inv_l), E::pack2(o[2] * inv_l, o[3] * inv_l)};
+  const int b = bh / H, h = bh - b * H;
+  *reinterpret_cast<u32x2*>(O + (((size_t)b * Nq + row) * H + h) * kD + 8 * quad + 4 * hh) = out;
+  if (LSE != nullptr && quad == 0 && hh == 0) LSE[(size_t)bh * Nq + row] = m * 0.69314718055994530942f + __builtin_logf(l);
+}
+
+template <int DT, int kD, int kWv> int launch(const Problem& p, const ShortPlan& plan, void* workspace) {
+  const int n_q = (p.Nq + kShortRows - 1) / kShortRows, heads = p.B * p.H, total = heads * plan.items;
+  ShortCut cut;
+  cut.items = plan.items;
+  if (plan.slices > 1) {
+    cut.part_o = static_cast<float*>(workspace);
+    cut.part_ml = cut.part_o + (size_t)heads * n_q * plan.slices * kShortRows * kD;
+    cut.chunk = plan.chunk;
+    cut.slices = plan.slices;
+  }
+  uint16_t* const o = static_cast<uint16_t*>(p.O);
   auto* kernel = fa2_short_kernel<DT, kD, kWv, true>;
   if constexpr (kWv > 2) {   // (two wavefronts: under the mask only)
     if (!p.causal) kernel = fa2_short_kernel<DT, kD, kWv, false>;
   }
-  return enqueue(kernel, total, kWv * 64, p.stream,
-                 static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.K), static_cast<const uint16_t*>(p.V),
-                 static_cast<uint16_t*>(p.O), p.LSE, p.H, p.Nq, p.Nk, p.scale_log2e, n_q, total);
+  const int rc = enqueue(kernel, total, kWv * 64, p.stream, static_cast<const uint16_t*>(p.Q), static_cast<const uint16_t*>(p.K),
+                         static_cast<const uint16_t*>(p.V), o, p.LSE, p.H, p.Nq, p.Nk, p.scale_log2e, n_q, total, cut);
+  if (rc != FA2_OK || plan.slices == 1) return rc;
+  return enqueue(p.causal ? fa2_short_merge_kernel<DT, kD, true> : fa2_short_merge_kernel<DT, kD, false>, heads * n_q * (kD / 32), 256,
+                 p.stream, cut, o, p.LSE, p.H, p.Nq, n_q);
 }
 
 }  // namespace
 
-int short_tiles(const Problem& p, int waves) {
+size_t short_workspace(int B, int H, int Nq, int d, const ShortPlan& plan) {
+  const size_t tiles = (size_t)B * H * ((Nq + kShortRows - 1) / kShortRows);
+  return plan.slices == 1 ? 0 : tiles * plan.slices * kShortRows * (d + 2) * sizeof(float);
+}
+
+int short_tiles(const Problem& p, const ShortPlan& plan, void* workspace) {
   auto go = [&](auto dt) {
     constexpr int kDT = decltype(dt)::value;
-    if (p.d == 256) return waves == 2 ? launch<kDT, 256, 2>(p) : launch<kDT, 256, 4>(p);
-    if (p.d == 128) return waves == 4 ? launch<kDT, 128, 4>(p) : launch<kDT, 128, 8>(p);
-    return waves == 4 ? launch<kDT, 64, 4>(p) : launch<kDT, 64, 8>(p);
+    if (p.d == 256) return plan.waves == 2 ? launch<kDT, 256, 2>(p, plan, workspace) : launch<kDT, 256, 4>(p, plan, workspace);
+    if (p.d == 128) return plan.waves == 4 ? launch<kDT, 128, 4>(p, plan, workspace) : launch<kDT, 128, 8>(p, plan, workspace);
+    return plan.waves == 4 ? launch<kDT, 64, 4>(p, plan, workspace) : launch<kDT, 64, 8>(p, plan, workspace);
   };
   return p.dtype == FA2_FP16 ? go(std::integral_constant<int, FA2_FP16>{}) : go(std::integral_constant<int, FA2_BF16>{});
 }
