@@ -11,6 +11,7 @@ SOURCES = [os.path.join(_PKG, "csrc", "fa2_fwd.hip")]                # the tile 
 SPLIT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_decode.hip"),       # one query per sequence, keys split
                  os.path.join(_PKG, "csrc", "fa2_split.hip")]        # few query tiles, keys split
 STAGE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_stage.hip")]        # d = 64 and 256, softmax mixed into the MFMAs
+WIDE_SOURCES = [os.path.join(_PKG, "csrc", "fa2_wide.hip")]          # d = 128, partial tiles, 256 rows per workgroup
 SHORT_SOURCES = [os.path.join(_PKG, "csrc", "fa2_short.hip")]        # few query rows in all
 INCLUDE = os.path.join(_ROOT, "include")
 LIBRARY = os.path.join(_PKG, "libfa2.so")
@@ -42,7 +43,7 @@ def build_library(verbose: bool = False) -> str:
     """Compile the HIP sources into ``libfa2.so`` and ``libfa2_probe.so`` and the call on torch tensors, which uses the
     former, into ``_fa2_torch.so``, next to this file; returns the former's path."""
     _hipcc(PROBE_SOURCES, PROBE_LIBRARY, verbose)
-    _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES], LIBRARY, verbose)
+    _hipcc([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES, *WIDE_SOURCES], LIBRARY, verbose)
     _build_torch_call(verbose)
     return LIBRARY
 
@@ -132,7 +133,7 @@ if __name__ == "__main__":
     import sys
 
     if "--resource-usage" in sys.argv:
-        rows = resource_usage([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES])
+        rows = resource_usage([*SOURCES, *SPLIT_SOURCES, *STAGE_SOURCES, *SHORT_SOURCES, *WIDE_SOURCES])
         print("| kernel | VGPRs | AGPRs | SGPRs | scratch B/lane | LDS B/workgroup | wavefronts/SIMD |")
         print("|---|---|---|---|---|---|---|")
         for k in sorted(rows, key=lambda r: r["name"]):

@@ -111,7 +111,7 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
     if (plan.slices > 1 && workspace_bytes < fa2::short_workspace(B, H, Nq, d, plan))
       plan = fa2::short_plan(B, H, Nq, Nk, d, p.causal, false);
     if (plan.waves != 0) return fa2::short_tiles(p, plan, workspace);
-    if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc)) return rc;
+    if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc) || fa2::wide_tiles(p, &rc)) return rc;
     variant = choose_variant(B, H, Nq, Nk, d, mask);
   }
   if (variant != FA2_VARIANT_NARROW) {

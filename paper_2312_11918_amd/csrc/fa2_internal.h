@@ -52,6 +52,10 @@ __attribute__((visibility("hidden"))) bool split_tiles(const Problem& p, void* w
 __attribute__((visibility("hidden"))) size_t short_workspace(int B, int H, int Nq, int d, const ShortPlan& plan);
 __attribute__((visibility("hidden"))) int short_tiles(const Problem& p, const ShortPlan& plan, void* workspace);
 
+// fa2_wide.hip: d = 128 on partial tiles in the 256-row shape.  Launches nothing and is false where another launch is the better
+// one; otherwise *rc is the launch's return code.
+__attribute__((visibility("hidden"))) bool wide_tiles(const Problem& p, int* rc);
+
 // fa2_stage.hip: d = 64 with 64 query rows per wavefront, and d = 256.  Launches nothing and is false where the tile kernel's
 // whole launch is the better one; otherwise *rc is the launch's return code.
 __attribute__((visibility("hidden"))) bool stage_tiles(const Problem& p, int* rc);

@@ -157,7 +157,7 @@ constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gf
 //
 // kRagged lifts the restriction to whole tiles: Nq query rows and Nk keys of any size >= 1.  Query rows past
 // Nq-1 are computed from a copy of the last row and not stored; K/V rows past Nk-1 are staged as copies of
-// the last row (finite data) and their columns of S are set to -inf in the last kNBuf tiles, the only ones
+// the last row (finite data; as zeros in the 256-row shape) and their columns of S are set to -inf in the last kNBuf tiles, the only ones
 // that can hold them; the tile count is rounded up to a multiple of kNBuf (a padding tile is fully masked).
 //
 // kSplit (with kRagged) is for problems whose Q tiles are too few to fill the chip.  Two cuts of the keys:
@@ -347,7 +347,8 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     // d = 64 with the causal mask and partial tiles has few to spare at three wavefronts per SIMD: here one offset per
     // operand is kept, and nothing for the last tiles (whose offsets the halves, with two per SIMD, may keep: 2 % at N = 638).
     constexpr bool kOneOffset = D == 64 && kCausal && kRagged;
-    if (kRagged && (j + 1) * kBc > Nk) {
+    // (the 256-row shape has no registers for these: the range check of the descriptor leaves zeros in LDS for such rows)
+    if (kRagged && !kFlagSync && (j + 1) * kBc > Nk) {
       if constexpr (kOneOffset && !kSplit) asm volatile("" : "+v"(lane));
       // a tile with rows past the last key: those rows are filled with copies of the last key's row, so LDS
       // holds finite numbers everywhere (their columns of S are masked; 0 * finite = 0 in GEMM-II)
@@ -783,8 +784,8 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     }
 
     // partial tiles: wavefronts whose rows all lie past the last query keep the boundaries and skip the arithmetic
-    // (not in the two partial-tile kernels that have no register left for one more condition)
-    constexpr bool kSkipDeadRows = kRagged && D <= 128 && !(D == 128 && kCausal);
+    // (not in the partial-tile kernels that have no register left for one more condition)
+    constexpr bool kSkipDeadRows = kRagged && D <= 128 && !(D == 128 && kCausal) && !kFlagSync;
     const bool rows_live = !kSkipDeadRows || qt * kRows + wave * 32 < Nq;   // wavefront-uniform
     int j = 0;
     for (; j + kNBuf < n_tiles; j += kNBuf) {  // every barrier of these iterations issues its full set of loads
@@ -916,7 +917,9 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
         // two stores of 16 rows x 64 bytes.  Only this wavefront touches its slab, and LDS executes a wavefront's
         // accesses in order, so no barrier is involved.
         uint16_t* slab = o_slab + wave_all * 1024;
-        const int rrow = lane >> 2, rchunk = lane & 3;   // as a reader: row (+16 for the second half), chunk
+        int lane_out = lane;
+        if constexpr (kFlagSync && kRagged) asm volatile("" : "+v"(lane_out));   // not kept through the loop: no registers
+        const int rrow = lane_out >> 2, rchunk = lane_out & 3;   // as a reader: row (+16 for the second half), chunk
         uint16_t* orow = O + head_base + (size_t)(qt * kRows + wave * 32 + rrow) * row_stride + 8 * rchunk + my_column;
 #pragma unroll
         for (int db = 0; db < kMyBlocks; ++db) {

@@ -1,0 +1,46 @@
+"""Partial tiles in the 256-row shape, without a GPU: which problems run so (the rule is plain C++, compiled here with the host
+compiler), on both sides of its lines, and the registers and LDS of its kernels."""
+import os
+import subprocess
+
+from paper_2312_11918_amd import build
+from test_gpu_wide import CASES
+
+PROGRAM = r"""
+#include <stdio.h>
+#include "fa2_wide_plan.h"
+int main() {
+  int B, H, Nq, Nk, d, causal;
+  while (scanf("%d %d %d %d %d %d", &B, &H, &Nq, &Nk, &d, &causal) == 6)
+    printf("%d\n", fa2::wide_accepts(B, H, Nq, Nk, d, causal != 0));
+}
+"""
+
+# B, H, Nq, Nk, d, causal; measured, see fa2_wide_plan.h
+TAKEN = [(8, 16, 2047, 2047, 128, 0), (16, 16, 1000, 1000, 128, 0), (32, 16, 511, 511, 128, 0), (8, 16, 2047, 3000, 128, 0),
+         (2, 16, 2000, 2000, 128, 0), (8, 16, 2047, 2047, 128, 1), (32, 16, 500, 500, 128, 1), (1, 16, 8100, 8100, 128, 1),
+         (8, 16, 2048, 1000, 128, 0)]
+LEFT = [(8, 16, 1900, 1900, 128, 0), (3, 16, 2000, 2000, 128, 0), (64, 16, 250, 250, 128, 0), (8, 16, 500, 5000, 128, 0),
+        (8, 16, 2048, 2048, 128, 0), (8, 16, 2047, 2047, 64, 0), (8, 16, 1500, 1500, 128, 1), (16, 16, 700, 700, 128, 1),
+        (65535, 65536, 2147483647, 5, 128, 0)]   # (and no overflow)
+
+
+def test_lines_of_the_rule(tmp_path):
+    source, program = tmp_path / "wide.cc", tmp_path / "wide"
+    source.write_text(PROGRAM)
+    csrc = os.path.dirname(build.SOURCES[0])
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(source), "-o", str(program)], check=True)
+    problems = TAKEN + [(B, H, Nq, Nk, 128, causal) for B, H, Nq, Nk, _, causal in CASES] + LEFT
+    text = "".join(" ".join(str(int(x)) for x in p) + "\n" for p in problems)
+    out = subprocess.run([str(program)], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.split()
+    for i, (p, got) in enumerate(zip(problems, out)):
+        assert got == ("1" if i < len(problems) - len(LEFT) else "0"), p
+
+
+def test_kernels_fit_their_launches():
+    kernels = build.resource_usage(build.WIDE_SOURCES)
+    assert len(kernels) == 4   # 2 element types, with and without the causal mask
+    for k in kernels:
+        assert "d=128, 8 wavefronts" in k["name"] and "partial tiles" in k["name"], k
+        assert k["scratch_bytes_per_lane"] == 0 and k["vgprs"] + k["agprs"] <= 256 and k["waves_per_simd"] >= 2, k
+        assert k["lds_bytes_per_workgroup"] <= 160 * 1024, k
