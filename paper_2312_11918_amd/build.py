@@ -109,7 +109,7 @@ def resource_usage(sources=SOURCES):
             continue
         m = re.search(r"fa2_stage_kernelILi(\d+)ELi(\d+)ELb(\d)ELb(\d)E", k["mangled"])
         if m:
-            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}, {m[3]} wavefronts{', causal' if m[4] == '1' else ''}"
+            k["name"] = (f"fa2_stage_kernel<{'fp16' if m[1] == '0' else 'bf16'}, d={m[2]}{', causal' if m[3] == '1' else ''}"
                          f"{', partial tiles' if m[4] == '1' else ''}>")
             continue
         m = re.search(r"fa2_short_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", k["mangled"])
