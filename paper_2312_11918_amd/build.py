@@ -60,7 +60,7 @@ def _build_torch_call(verbose):
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            f'-DFA2_TORCH_VERSION="{torch.__version__}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-isystem{p}" for p in includes), TORCH_SOURCE,
-           "-o", TORCH_LIBRARY, f"-L{_PKG}", "-l:libfa2.so", f"-L{torch_lib}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-o", TORCH_LIBRARY, f"-L{_PKG}", "-l:libfa2.so", f"-L{torch_lib}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python",
            f"-L{os.path.join(rocm, 'lib')}", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
