@@ -5,8 +5,8 @@
 // (1.0 us per K/V tile at d = 128).  Here the keys of a Q tile are cut into halves inside a workgroup of eight wavefronts
 // (d <= 128; 1.3 us per PAIR of tiles), and, where the caller gives a workspace, into slices over workgroups whose partial
 // results a second kernel on the same stream merges.  The price is that kernel (5 us) and the partial O in fp32, written
-// and read once (64 KiB per workgroup at d = 128).  B1 H16 Nq512 Nk8192 d128: 129 us whole, 41 here; B1 H16 N1111 d128
-// causal, in one launch: 29 and 19.
+// and read once (64 KiB per workgroup at d = 128).  B1 H16 Nq512 Nk8192 d128: 129 us whole, 41 here; B1 H12 N3088 d128
+// causal, in one launch: 64 and 45.  (Fewer query rows than that are fa2_short.hip's: tiles of 32.)
 #include "fa2_split_plan.h"
 #include "fa2_tile_kernel.h"
 
