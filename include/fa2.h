@@ -163,9 +163,9 @@ size_t fa2_workspace_bytes(int B, int H, int Nq, int Nk, int d, int mask);
  * only: nothing is launched and no HIP call is made.  Returns the FA2_VARIANT_* value (> 0), or a negative
  * FA2_ERR_* for sizes, head dimensions or masks that the entry points refuse.  (A single query row, Nq == 1, runs in
  * a kernel of its own that has no query tiles, problems of few query rows in all in one with 32 rows per workgroup, problems of
- * few Q tiles in a form of the 128-row shape with the keys
- * cut, most of many at d = 64 in a kernel with 64 rows per wavefront, 256 per workgroup and two workgroups per CU, and
- * most at d = 256 in a kernel with 128 rows per workgroup and K/V stages of 32 keys; the value returned is the tile
+ * few Q tiles in a form of the 128-row shape with the keys cut, most of many at d = 64 in a kernel with 64 rows per wavefront,
+ * 256 per workgroup and two workgroups per CU, most at d = 256 in a kernel with 128 rows per workgroup and K/V stages of 32 keys,
+ * and partial tiles at d = 128 that fill whole rounds of the CUs in a form of the 256-row shape; the value returned is the tile
  * shape they would otherwise get.)
  */
 int fa2_tile_shape(int B, int H, int Nq, int Nk, int d, int mask);
