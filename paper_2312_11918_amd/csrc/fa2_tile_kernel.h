@@ -29,9 +29,11 @@
 #include <utility>
 
 #include "fa2_internal.h"
+#include "fa2_wide_plan.h"
 
 using fa2::enqueue;
 using fa2::kCUs;
+using fa2::wide_stages_tile;
 
 namespace {
 
@@ -347,6 +349,9 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     // d = 64 with the causal mask and partial tiles has few to spare at three wavefronts per SIMD: here one offset per
     // operand is kept, and nothing for the last tiles (whose offsets the halves, with two per SIMD, may keep: 2 % at N = 638).
     constexpr bool kOneOffset = D == 64 && kCausal && kRagged;
+    if constexpr (kRagged && kFlagSync) {
+      if (!wide_stages_tile(j, Nk)) return;   // (wavefront-uniform; every wait of this shape is for all loads, however many)
+    }
     // (the 256-row shape has no registers for these: the range check of the descriptor leaves zeros in LDS for such rows)
     if (kRagged && !kFlagSync && (j + 1) * kBc > Nk) {
       if constexpr (kOneOffset && !kSplit) asm volatile("" : "+v"(lane));

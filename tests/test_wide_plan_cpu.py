@@ -37,6 +37,47 @@ def test_lines_of_the_rule(tmp_path):
         assert got == ("1" if i < len(problems) - len(LEFT) else "0"), p
 
 
+STAGED = r"""
+#include <stdio.h>
+#include "fa2_wide_plan.h"
+int main() {
+  int j, Nk;
+  while (scanf("%d %d", &j, &Nk) == 2) printf("%d\n", fa2::wide_stages_tile(j, Nk));
+}
+"""
+
+
+def _in_range(lane_offset, scalar_offset, num_records):
+    """The range check of a raw buffer load, in the unsigned 32-bit arithmetic that it is specified in."""
+    return lane_offset < (num_records - scalar_offset) % 2 ** 32
+
+
+def test_no_row_past_the_last_key_passes_the_range_check(tmp_path):
+    source, program = tmp_path / "staged.cc", tmp_path / "staged"
+    source.write_text(STAGED)
+    csrc = os.path.dirname(build.SOURCES[0])
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(source), "-o", str(program)], check=True)
+    # every count of keys that wide_accepts() takes, at both ends of the counts of tiles
+    counts = [n for n in (*range(1, 1300), *range(8000, 8300)) if (n + 127) // 128 % 2 == 0]
+    tiles = [(j, n) for n in counts for j in range((n + 255) // 256 * 4)]   # padded to whole rounds of the four buffers
+    text = "".join(f"{j} {n}\n" for j, n in tiles)
+    out = subprocess.run([str(program)], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.split()
+    assert len(out) == len(tiles)
+    wrapping = 0
+    for (j, n), staged in zip(tiles, out):
+        assert (staged == "1") == (64 * j < n)   # all tiles with a key
+        for heads in (1, 16):
+            row_bytes = 256 * heads
+            num_records, at = (n - 1) * row_bytes + 256, 64 * j * row_bytes
+            rows = [64 * j + i for i in (0, 1, 31, 63)] + [n - 1, n]
+            for row in (x for x in rows if 64 * j <= x < 64 * j + 64):
+                read = _in_range((row - 64 * j) * row_bytes, at, num_records)
+                if staged == "1":
+                    assert read == (row < n), (j, n, row)
+                wrapping += read and row >= n
+    assert wrapping > 0   # what a request for a tile without keys would read
+
+
 def test_kernels_fit_their_launches():
     kernels = build.resource_usage(build.WIDE_SOURCES)
     assert len(kernels) == 4   # 2 element types, with and without the causal mask
