@@ -108,8 +108,13 @@ int run(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
     if (fa2::decode_accepts(B, H, Nq)) return fa2::decode(p, workspace, workspace_bytes);
     int rc;
     fa2::ShortPlan plan = fa2::short_plan(B, H, Nq, Nk, d, p.causal, workspace != nullptr);
-    if (plan.slices > 1 && workspace_bytes < fa2::short_workspace(B, H, Nq, d, plan))
+    if (plan.slices > 1 && workspace_bytes < fa2::short_workspace(B, H, Nq, d, plan)) {
+      // too little is as good as none, also for slices of 128 rows, which may take less (B1 H1 Nq128 Nk8000 d64: 540672 bytes
+      // of 946176): what a call computes does not depend on how much it was given
+      workspace = nullptr;
+      workspace_bytes = 0;
       plan = fa2::short_plan(B, H, Nq, Nk, d, p.causal, false);
+    }
     if (plan.waves != 0) return fa2::short_tiles(p, plan, workspace);
     if (fa2::split_tiles(p, workspace, workspace_bytes, &rc) || fa2::stage_tiles(p, &rc) || fa2::wide_tiles(p, &rc)) return rc;
     variant = choose_variant(B, H, Nq, Nk, d, mask);

@@ -132,6 +132,10 @@ def test_keys_masked_by_the_lowest_value(Nq, Nk, live, d, sliced, workspace):
     (1, 6, 3000, 3000, 128, True),
     (1, 4, 300, 3000, 256, False),
     (1, 8, 1, 4096, 128, False),     # the single-query kernel
+    (1, 1, 128, 8000, 64, False),    # slices of 32 rows in that many bytes; slices of 128 rows would take 540672
+    (1, 2, 100, 8000, 256, False),
+    (1, 2, 256, 2000, 64, False),    # a byte less: the same kernel in one slice
+    (3, 1, 1024, 1024, 128, True),
 ])
 def test_workspace_one_byte_short_and_exact(B, H, Nq, Nk, d, causal):
     # a byte less than fa2_workspace_bytes(): exactly fa2_fwd_qk, the workspace untouched; exactly that many: not a byte
