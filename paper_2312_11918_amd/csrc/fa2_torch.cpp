@@ -49,10 +49,17 @@ struct WithoutGil {
 // Device memory from the allocator that torch's own factory functions use, without their way through the dispatcher: O and LSE
 // took 1.1 us of a call's 4.9 so, 0.5 now (B1 H2 N256 d64; the kernel takes 4.4).  Where something has asked to see dispatched calls
 // (a transform, a trace), they are made.
+bool calls_are_seen() { return !(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty(); }
+
 at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, c10::Device device) {
-  const c10::DispatchKeySet asked = c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set;
-  if (!asked.empty()) return at::empty(sizes, at::TensorOptions().dtype(type).device(device));
+  if (calls_are_seen()) return at::empty(sizes, at::TensorOptions().dtype(type).device(device));
   return at::Tensor(at::detail::empty_cuda(sizes, type, device, std::nullopt));
+}
+
+// ... with the strides of t too: those of sizes of one may be any
+at::Tensor empty_as(const at::Tensor& t) {
+  if (calls_are_seen()) return at::empty_like(t);
+  return at::Tensor(at::detail::empty_strided_cuda(t.sizes(), t.strides(), t.scalar_type(), t.device()));
 }
 
 // forward(q, k, v, scale, out, lse, return_lse, causal): (O, LSE), or the library's error code, or None
@@ -110,7 +117,7 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   {
     // (an allocation waits for the driver at times, a launch where the queue is full)
     const WithoutGil released;
-    if (!out.defined()) out = empty(q.sizes(), type, device);
+    if (!out.defined()) out = empty_as(q);
     if (return_lse && !lse.defined()) lse = empty({B, H, Nq}, at::kFloat, device);
     // Scratch of the launch stream: dropped on return, its memory is handed out again only behind this call's kernels.  Without
     // it the call still runs, its keys unsplit.

@@ -143,6 +143,25 @@ def test_surroundings():
     assert results == [True] * 4
 
 
+@pytest.mark.parametrize("shape,strides", [
+    ((1, 100, 2, 64), (12800, 128, 64, 1)),
+    ((1, 100, 2, 64), (5, 128, 64, 1)),           # the stride of a size of one says nothing about where elements are
+    ((2, 1, 4, 128), (512, 1, 128, 1)),           # ... as of one new query per sequence, cut from a channels-last tensor
+    ((1, 1, 1, 64), (3, 7, 11, 1)),
+])
+def test_the_output_has_the_strides_of_the_query(shape, strides):
+    print(f"torch call: strides {strides}", flush=True)
+    torch = torch_gpu()
+    q = torch.randn(12800, device="cuda").half().as_strided(shape, strides)
+    k = torch.randn((shape[0], 77, *shape[2:]), device="cuda").half()
+    assert q.is_contiguous()
+    ref, ref_lse = fa2.fa2_fwd(q, k, k, 0.125, stream=torch.cuda.current_stream())
+    assert ref.stride() == strides
+    o, lse = _native(q, k, k, 0.125, None, None, True, False)
+    assert o.stride() == ref.stride() and lse.stride() == ref_lse.stride()
+    assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
+
+
 # Loaded as torch's allocator in a process of its own: whether the thread that allocates holds the interpreter's lock.
 ALLOCATOR = r"""
 #include <Python.h>
