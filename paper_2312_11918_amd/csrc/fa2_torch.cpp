@@ -13,6 +13,7 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
@@ -48,8 +49,11 @@ struct WithoutGil {
 
 // Device memory from the allocator that torch's own factory functions use, without their way through the dispatcher: O and LSE
 // took 1.1 us of a call's 4.9 so, 0.5 now (B1 H2 N256 d64; the kernel takes 4.4).  Where something has asked to see dispatched calls
-// (a transform, a trace), they are made.
-bool calls_are_seen() { return !(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty(); }
+// (a transform, a trace, a profiler's record of operators), they are made.
+bool calls_are_seen() {
+  return !(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() ||
+         at::getStepCallbacksUnlessEmpty(at::RecordScope::FUNCTION).has_value();
+}
 
 at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, c10::Device device) {
   if (calls_are_seen()) return at::empty(sizes, at::TensorOptions().dtype(type).device(device));

@@ -162,6 +162,22 @@ def test_the_output_has_the_strides_of_the_query(shape, strides):
     assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
 
 
+def test_allocations_that_something_watches():
+    # what sees dispatched calls sees those of the Python path
+    print("torch call: watched", flush=True)
+    torch = torch_gpu()
+    q, k, v = _inputs(1, 4, 200, 4096, 64)   # O, LSE and scratch memory
+    ref = fa2.fa2_fwd(q, k, v, 0.125)[0]
+    traced = torch.jit.trace(lambda *x: fa2.fa2_fwd(*x, 0.125), (q, k, v), check_trace=False)
+    kinds = [n.kind() for n in traced.graph.nodes()]
+    assert kinds.count("aten::empty_like") == 1 and kinds.count("aten::empty") == 1, kinds   # (no scratch: nothing returns it)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as profile:
+        o = _native(q, k, v, 0.125, None, None, True, False)[0]
+    names = [e.name for e in profile.events()]
+    assert names.count("aten::empty_like") == 1 and names.count("aten::empty") == 2, names
+    assert torch.equal(o, ref)
+
+
 # Loaded as torch's allocator in a process of its own: whether the thread that allocates holds the interpreter's lock.
 ALLOCATOR = r"""
 #include <Python.h>
