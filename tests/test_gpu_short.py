@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from test_gpu_ragged import _check, _make, _run
-from _gpu_common import TOL_O_MAX, mask_by_lowest_value, torch_gpu
+from _gpu_common import TOL_O_MAX, TOL_O_MEAN, mask_by_lowest_value, torch_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -52,13 +52,18 @@ def test_short_parity(B, H, Nq, Nk, d, dtype, causal, outliers, waves, slices):
     qb, kb, vb = _make(B, H, Nq, Nk, d, dtype, 52000 + Nq + Nk + d, outliers)
     scale = float(np.float32(d) ** np.float32(-0.5))
     o_ref, lse_ref = oracle.attention(*(oracle.widen(x, dtype) for x in (qb, kb, vb)), scale, causal=causal)
-    o, lse = _run(qb, kb, vb, dtype, scale, causal)
-    # P and O are rounded to the 16-bit type: each is off by up to 2^-8 of its value in bf16, so an output beyond 2.56 / 2 (the first
-    # rows under the mask, which have few keys to average) may be off by more than the 1e-2 of the other tests, by 2^-7 |O|
-    fits = np.abs(o - o_ref) <= np.maximum(TOL_O_MAX, np.abs(o_ref) * 2.0 ** -7)
-    assert np.all(fits), f"max |dO| {np.abs(o - o_ref).max():.3e}"
-    large = np.abs(o_ref) * 2.0 ** -7 > TOL_O_MAX
-    _check(np.where(large, o_ref, o), lse, o_ref, lse_ref, "short")
+    first = o, lse = _run(qb, kb, vb, dtype, scale, causal)
+    if dtype == "bf16":
+        # P and O are rounded to bf16, each off by up to 2^-8 of its value, so an output beyond 2.56 / 2 (the first rows under the mask,
+        # which have few keys to average) may be off by more than the 1e-2 of the other tests, by 2^-7 |O|.  The mean bound is
+        # for all elements as they are.
+        large = np.abs(o_ref) * 2.0 ** -7 > TOL_O_MAX
+        eo = np.abs(o - o_ref)
+        assert np.all(np.isfinite(o)) and np.all(eo[large] <= np.abs(o_ref)[large] * 2.0 ** -7), f"max |dO| {eo.max():.3e}"
+        assert eo.mean() <= TOL_O_MEAN, f"mean |dO| {eo.mean():.3e}"
+        o = np.where(large, o_ref, o)   # (what is left of the bound of 1e-2)
+    _check(o, lse, o_ref, lse_ref, "short")
+    o, lse = first
     again, lse_again = _run(qb, kb, vb, dtype, scale, causal)
     assert np.array_equal(o, again) and np.array_equal(lse, lse_again)   # summed in one order, whoever ends first
 
