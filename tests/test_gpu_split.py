@@ -1,5 +1,6 @@
-"""GPU parity of the launches that cut the keys (few Q tiles): halves inside a workgroup, slices over workgroups and their
-merge, against the fp64 CPU oracle on guarded buffers, with the tolerances of the whole launches."""
+"""GPU parity of the launches that cut the keys (few Q tiles): over the wavefronts of a workgroup, over workgroups and their
+merge, against the fp64 CPU oracle on guarded buffers, with the tolerances of the whole launches.  Which launch each case gets is in
+test_routes_cpu.py; most of these get tiles of 32 rows, and test_gpu_launches.py has more of those that keep 128."""
 import ctypes
 
 import numpy as np
@@ -12,25 +13,25 @@ from _gpu_common import mask_by_lowest_value, torch_gpu
 
 pytestmark = pytest.mark.gpu
 
-# B, H, Nq, Nk, d, dtype, causal, outliers, sliced: sizes at the edges of a half (64 keys), a step of both (128), the padding
-# to four tiles, and a slice; the last slice with one tile, with a part of one; Q tiles with dead wavefronts
+# B, H, Nq, Nk, d, dtype, causal, outliers, sliced (over workgroups): sizes at the edges of tiles of 64 keys, pairs and fours of
+# them, and of slices; Q tiles with dead wavefronts
 CASES = [
     (1, 2, 129, 1500, 128, "fp16", False, 0.0, True),
-    (1, 2, 128, 641, 128, "bf16", False, 0.0, False),     # 12 tiles, the last pair with one key
+    (1, 2, 128, 641, 128, "bf16", False, 0.0, False),     # a last tile of one key
     (2, 3, 100, 2000, 64, "fp16", False, 0.02, True),
-    (1, 8, 33, 4097, 128, "bf16", False, 0.0, True),     # slices; the last one starts the last pair of tiles
+    (1, 8, 33, 4097, 128, "bf16", False, 0.0, True),      # a last block of one key
     (1, 1, 2, 16384, 64, "fp16", False, 0.0, True),
     (1, 1, 31, 5000, 256, "bf16", False, 0.0, True),
     (1, 4, 300, 3000, 256, "fp16", False, 0.01, True),
-    (2, 8, 1024, 1024, 128, "fp16", False, 0.0, False),  # halves only
+    (2, 8, 1024, 1024, 128, "fp16", False, 0.0, False),  # halves
     (2, 24, 200, 1500, 64, "bf16", False, 0.0, False),
     (1, 16, 1111, 1111, 128, "bf16", True, 0.0, False),
     (2, 2, 321, 321, 64, "fp16", True, 0.0, False),
-    (1, 6, 3000, 3000, 128, "fp16", True, 0.01, True),   # causal slices: the first Q tiles lie in one slice
+    (1, 6, 3000, 3000, 128, "fp16", True, 0.01, True),   # slices of 128-row tiles: the first Q tiles lie in one slice
     (1, 3, 1500, 1500, 64, "bf16", True, 0.0, True),
     (1, 2, 1409, 1409, 256, "fp16", True, 0.0, True),    # a last Q tile of one row
     (1, 2, 640, 640, 128, "fp16", True, 0.0, False),
-    (2, 24, 665, 665, 128, "bf16", True, 0.0, False),    # more Q tiles than CUs: longest first
+    (2, 24, 665, 665, 128, "bf16", True, 0.0, False),    # halves, more Q tiles than CUs: longest first
     (6, 16, 400, 400, 256, "fp16", True, 0.0, False),
     (5, 11, 897, 897, 64, "fp16", True, 0.0, False),     # heads not a multiple of 8
 ]
@@ -62,7 +63,7 @@ def test_split_parity(B, H, Nq, Nk, d, dtype, causal, outliers, sliced):
     assert bool((small == 255).all())
 
 
-@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128)])
+@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128), (1100, 4096, 128)])
 def test_split_on_another_stream_and_in_a_graph(Nq, Nk, d):
     # the workspace belongs to the launch stream, or to the graph's pool: bits as on the current stream
     torch = torch_gpu()
@@ -92,16 +93,16 @@ def test_split_on_another_stream_and_in_a_graph(Nq, Nk, d):
 
 
 @pytest.mark.parametrize("Nq,Nk,live,d,sliced", [
-    (128, 641, 40, 128, False),    # half 1 sees masked keys only
+    (128, 641, 40, 128, False),    # wavefronts that see masked keys only
     (100, 2000, 64, 64, True),     # ... and slices that do
     (128, 1024, 1, 128, True),
     (64, 8192, 5000, 128, True),
-    (200, 4000, 64, 256, True),    # slices without halves
+    (200, 4000, 64, 256, True),
 ])
 @pytest.mark.parametrize("workspace", [True, False])
 def test_keys_masked_by_the_lowest_value(Nq, Nk, live, d, sliced, workspace):
     # scaled logits of masked keys overflow fp32 (lowest bf16 * log2 e); the inputs are finite, so O and LSE are those of the
-    # live keys, also where a half or a slice holds none
+    # live keys, also where a wavefront, a half or a slice holds none
     print(f"split masked keys Nq={Nq} Nk={Nk} live={live} d={d} workspace={workspace}", flush=True)
     torch = torch_gpu()
     assert (fa2.fa2_workspace_bytes(1, 2, Nq, Nk, d) > 0) == sliced
@@ -127,7 +128,7 @@ def test_keys_masked_by_the_lowest_value(Nq, Nk, live, d, sliced, workspace):
 
 
 @pytest.mark.parametrize("B,H,Nq,Nk,d,causal", [
-    (1, 1, 128, 1430, 64, False),    # six slices with the whole workspace; three would fit in a byte less
+    (1, 1, 128, 1430, 64, False),    # five slices with the whole workspace; four would fit in a byte less
     (1, 16, 512, 8192, 128, False),
     (1, 6, 3000, 3000, 128, True),
     (1, 4, 300, 3000, 256, False),
@@ -170,7 +171,7 @@ def test_workspace_one_byte_short_and_exact(B, H, Nq, Nk, d, causal):
     assert bool((o.float() - o_ref.float()).abs().max() <= 2e-3) and bool((lse - lse_ref).abs().max() <= 1e-5)
 
 
-@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128)])
+@pytest.mark.parametrize("Nq,Nk,d", [(256, 4096, 128), (1, 4096, 128), (1100, 4096, 128)])
 def test_capture_begun_without_torch_holds_no_pool_memory(Nq, Nk, d):
     # nothing keeps torch's ordinary memory for such a graph: the call must leave its keys unsplit rather than take scratch
     # that other tensors own when the graph is replayed

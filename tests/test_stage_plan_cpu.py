@@ -1,4 +1,5 @@
-"""Which problems run with the softmax mixed into the MFMAs, and the compiled form of that kernel, on the CPU."""
+"""Which problems run with the softmax mixed into the MFMAs, of those that are not of few query rows (test_routes_cpu.py), and the
+compiled form of that kernel, on the CPU."""
 import os
 import subprocess
 
