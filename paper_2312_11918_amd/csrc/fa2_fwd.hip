@@ -76,7 +76,8 @@ int choose_variant(int B, int H, int Nq, int Nk, int d, int mask) {
   // below N = 2048 its two wavefronts per SIMD against three lose 2-5 %; what stage_accepts() leaves of d = 64 has one
   // round of it, so that it chains there in an explicit choice only).  With many rounds that are not whole it
   // still gains at d = 128 from N = 2048 on; with few, the 128-row shape, two workgroups per CU, spreads the
-  // remainder better.  d = 256 and partial tiles exist in the 128-row shape only.
+  // remainder better.  d = 256 exists in the 128-row shape only, partial tiles in the 256-row shape in fa2_wide.hip's
+  // launches only, which come before this choice.
   // Under the causal mask (one workgroup per pair of Q tiles, no chaining) it gains 1-3 % at d = 128 from N = 2048 on.
   const bool causal = mask == FA2_MASK_CAUSAL;
   const long long qt256 = Nq / kRows256;

@@ -6,9 +6,13 @@
 // wavefront, and the wavefronts are merged through LDS at the end.  A wavefront stages its own blocks of 32 keys, and nobody
 // else reads them, so the loop has no barrier and waits for nothing but the wavefront's own loads.
 //
-// The bound, beside the chain, is the path into LDS: every 32 rows read all of their keys, 128 KiB per 256 keys at d = 128, for
-// which a CU takes 1.4 us (90 GB/s; 0.75 us at d = 64).  MFMAs are busy a third of that time.  So the kernel is for problems
-// whose tiles are about one per CU (short_waves() has the lines and both sides); from there on 128 rows per tile read less.
+// The bound of the loop is the path into LDS, 81 GB/s and CU, for every 32 rows read all of their keys: a block per wavefront is 64
+// KiB at d = 128 and takes 0.81 us with one workgroup on a CU; at d = 64, half as much, 0.61 us with one (a block's own chain) and
+// 0.41 each with two.  The matrix cores need 0.22 us of the 0.81.  The rest of a call is launch, first loads and merge: B1 H16 N512
+// d128, four blocks per wavefront, is 3.3 us of loop in 7.8, the matrix cores busy in 12 % of the cycles of busy CUs, 15 bytes into
+// LDS in each (35 are 81 GB/s at 2.3 GHz); B1 H16 N1111 causal, up to nine blocks, has 19 % and 24 bytes.  No bank conflicts.  So
+// the kernel is for problems whose tiles are about one per CU (short_waves() has the lines and both sides); from there on 128 rows
+// per tile read less.
 // us a call, 128-row launches before / this kernel: B1 H2 N256 d64 5.7 / 4.4; B1 H16 N1111 d128 causal 19.7 / 15.3; B1 H24 N205
 // causal d = 64, 128, 256 10.4 / 4.6, 14.4 / 6.3, 24.0 / 10.9; B1 H2 N1111 d64 13.8 / 7.6; B3 H8 N193 d256 14.7 / 11.4; B1 H2 Nq35
 // Nk534 d128 11.7 / 8.0.

@@ -30,8 +30,9 @@ struct ShortPlan {
 //    27.8 / 31.1; d = 64: H48 Nq100 Nk4000 24.7 / 33.7.
 // Four wavefronts, of which two workgroups share a CU at d = 128 and four at d = 64, are ahead of eight but where few workgroups
 // have many keys each: 12.3 / 12.5 us for eight / four at B1 H1 N1300 d128 causal, 7.5 / 8.3 at B1 H4 N1000 d64, 6.7 / 6.9 at N768,
-// 5.7 / 5.6 at N512.  At d = 256 square problems of few tiles without the mask stay with the staged kernel, 13...22 % behind (H4 N384
-// 16.0 / 13.0), because it gives the bits of an explicit tile shape (fa2_fwd_variant), which a sum in parts cannot.  d = 256:
+// 5.7 / 5.6 at N512.  At d = 256 square problems of up to 64 tiles without the mask stay with the staged kernel, 13...22 % behind (H4
+// N384 16.0 / 13.0): no measurement draws that line.  It keeps small problems of this kind on the bits of an explicit tile shape
+// (fa2_fwd_variant), with which they are compared; a sum in parts has others, as problems of more tiles do here.  d = 256:
 // four, with two its workgroups fit twice on a CU (H96 N160 causal 18.1 / 14.2, 23.8 before).
 inline int short_waves(long long tiles, int Nq, int Nk, int d, bool causal) {
   const bool one_pair = Nk > 128 && Nk <= 256;   // causal: a pair of Q tiles of 128 rows

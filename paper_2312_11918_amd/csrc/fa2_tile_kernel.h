@@ -149,7 +149,9 @@ constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gf
 //                            its loop (arrival counters in LDS, see kFlagSync), takes `chain` Q tiles per
 //                            workgroup over one running K/V stream (see kChain) and stores O as pieces of rows.
 // Either way a SIMD runs two wavefronts, so one wavefront's softmax arithmetic overlaps the other's MFMAs.
-// `total_tiles` is the number of workgroups; `chain` is 1 except for unmasked launches of the 8-wavefront shape.
+// The second has a form for partial tiles (kRagged) at d = 128 (fa2_wide.hip), the first a form with the keys cut (kSplit).
+// `total_tiles` is the number of workgroups; `chain` is more than 1 where whole rounds of the CUs are chained: in the 8-wavefront
+// shape, and at d = 256 on whole tiles.
 //
 // kCausal applies the optional mask of S (Section 2 of the paper: entries of S may be set to -inf before the
 // softmax; here those with key index > query index).  A Q tile then stops at its diagonal: it visits
@@ -160,7 +162,8 @@ constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gf
 // kRagged lifts the restriction to whole tiles: Nq query rows and Nk keys of any size >= 1.  Query rows past
 // Nq-1 are computed from a copy of the last row and not stored; K/V rows past Nk-1 are staged as copies of
 // the last row (finite data; as zeros in the 256-row shape) and their columns of S are set to -inf in the last kNBuf tiles, the only ones
-// that can hold them; the tile count is rounded up to a multiple of kNBuf (a padding tile is fully masked).
+// that can hold them; the tile count is rounded up to a multiple of kNBuf (a padding tile's arithmetic is left out, in the 256-row
+// shape its loads too).
 //
 // kSplit (with kRagged) is for problems whose Q tiles are too few to fill the chip.  Two cuts of the keys:
 //  * d <= 128: a workgroup of eight wavefronts for 128 rows.  Wavefronts 0-3 (half 0) take the even K/V tiles, 4-7
