@@ -33,7 +33,7 @@
 
 using fa2::enqueue;
 using fa2::kCUs;
-using fa2::wide_stages_tile;
+using fa2::wide_staged_tile;
 
 namespace {
 
@@ -162,8 +162,7 @@ constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gf
 // kRagged lifts the restriction to whole tiles: Nq query rows and Nk keys of any size >= 1.  Query rows past
 // Nq-1 are computed from a copy of the last row and not stored; K/V rows past Nk-1 are staged as copies of
 // the last row (finite data; as zeros in the 256-row shape) and their columns of S are set to -inf in the last kNBuf tiles, the only ones
-// that can hold them; the tile count is rounded up to a multiple of kNBuf (a padding tile's arithmetic is left out, in the 256-row
-// shape its loads too).
+// that can hold them; the tile count is rounded up to a multiple of kNBuf (a padding tile's arithmetic is left out).
 //
 // kSplit (with kRagged) is for problems whose Q tiles are too few to fill the chip.  Two cuts of the keys:
 //  * d <= 128: a workgroup of eight wavefronts for 128 rows.  Wavefronts 0-3 (half 0) take the even K/V tiles, 4-7
@@ -352,9 +351,7 @@ __global__ __launch_bounds__(kWv * 64, kWv == 4 && D == 64 ? 3 : kWv == 4 && D <
     // d = 64 with the causal mask and partial tiles has few to spare at three wavefronts per SIMD: here one offset per
     // operand is kept, and nothing for the last tiles (whose offsets the halves, with two per SIMD, may keep: 2 % at N = 638).
     constexpr bool kOneOffset = D == 64 && kCausal && kRagged;
-    if constexpr (kRagged && kFlagSync) {
-      if (!wide_stages_tile(j, Nk)) return;   // (wavefront-uniform; every wait of this shape is for all loads, however many)
-    }
+    if constexpr (kRagged && kFlagSync) j = wide_staged_tile(j, Nk);
     // (the 256-row shape has no registers for these: the range check of the descriptor leaves zeros in LDS for such rows)
     if (kRagged && !kFlagSync && (j + 1) * kBc > Nk) {
       if constexpr (kOneOffset && !kSplit) asm volatile("" : "+v"(lane));

@@ -3,7 +3,7 @@
 // Sizes that are no whole tiles ran in the 128-row shape, which sends twice the bytes per FLOP from the L2 into LDS and pays a
 // prologue and an epilogue for every Q tile.  The 256-row kernel has no register left for a second set of source offsets, those
 // of the tiles with rows past the last key.  None is needed: the descriptor's range check turns such rows into zeros in LDS (as good
-// as copies of the last key: their columns of S are masked; a tile without any key is not loaded, see wide_stages_tile), and what
+// as copies of the last key: their columns of S are masked; a tile without any key is not asked for, see wide_staged_tile), and what
 // the epilogue derives from the lane is not kept through the loop.  256 registers, no scratch.  Without the mask the bits are those
 // of the 128-row shape; under it that one takes the row maximum on every one of its last tiles, this one only on those that the
 // diagonal crosses, so where a reference point moves there the last bits differ.  3.5 % at B8 H16 N2047 (258 -> 249 us, 1058 -> 1096

@@ -22,11 +22,12 @@ inline bool wide_accepts(int B, int H, int Nq, int Nk, int d, bool causal) {
   return groups <= 0x7fffffffLL && groups % kCUs == 0 && (groups >= 2 * kCUs || Nq >= 1024);
 }
 
-// Whether the 256-row shape on partial tiles loads K/V tile j (of 64 keys) into LDS.  Rows past the last key are left to the
-// descriptor's range check, which is specified as lane offset >= range - scalar offset: the scalar offset, that of the tile's first
-// row, has to lie within the range itself, past which the difference would wrap.  So a tile without any key, which only
-// rounds the count up to four, is not requested (nor is its arithmetic done).
-constexpr bool wide_stages_tile(int j, int Nk) { return j * 64LL < Nk; }
+// The K/V tile (of 64 keys) that the 256-row shape on partial tiles loads as tile j.  Rows past the last key are left to the descriptor's
+// range check, which is specified as lane offset >= range - scalar offset: the scalar offset, that of the tile's first row, has to
+// lie within the range itself, past which the difference would wrap.  So a tile without any key, which only rounds the count up
+// to four and whose arithmetic is left out, takes the last tile with one.  (Not loading it at all costs a branch per load
+// burst: B8 H16 N2047 256.6 -> 258.4 us; this one is within the noise of no check, 256.3.)
+constexpr int wide_staged_tile(int j, int Nk) { return j < (Nk - 1) / 64 ? j : (Nk - 1) / 64; }
 
 }  // namespace fa2
 #endif  // FA2_WIDE_PLAN_H_

@@ -42,7 +42,7 @@ STAGED = r"""
 #include "fa2_wide_plan.h"
 int main() {
   int j, Nk;
-  while (scanf("%d %d", &j, &Nk) == 2) printf("%d\n", fa2::wide_stages_tile(j, Nk));
+  while (scanf("%d %d", &j, &Nk) == 2) printf("%d\n", fa2::wide_staged_tile(j, Nk));
 }
 """
 
@@ -64,18 +64,19 @@ def test_no_row_past_the_last_key_passes_the_range_check(tmp_path):
     out = subprocess.run([str(program)], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.split()
     assert len(out) == len(tiles)
     wrapping = 0
-    for (j, n), staged in zip(tiles, out):
-        assert (staged == "1") == (64 * j < n)   # all tiles with a key
+    for (j, n), staged in zip(tiles, map(int, out)):
+        assert staged == j or 64 * j >= n   # all tiles with a key as they are
         for heads in (1, 16):
             row_bytes = 256 * heads
-            num_records, at = (n - 1) * row_bytes + 256, 64 * j * row_bytes
-            rows = [64 * j + i for i in (0, 1, 31, 63)] + [n - 1, n]
-            for row in (x for x in rows if 64 * j <= x < 64 * j + 64):
-                read = _in_range((row - 64 * j) * row_bytes, at, num_records)
-                if staged == "1":
-                    assert read == (row < n), (j, n, row)
-                wrapping += read and row >= n
-    assert wrapping > 0   # what a request for a tile without keys would read
+            num_records = (n - 1) * row_bytes + 256
+            for tile in {staged, j}:
+                at = 64 * tile * row_bytes
+                for row in {64 * tile + i for i in (0, 1, 31, 63)} | ({n - 1, n} & set(range(64 * tile, 64 * tile + 64))):
+                    read = _in_range((row - 64 * tile) * row_bytes, at, num_records)
+                    if tile == staged:
+                        assert read == (row < n), (j, n, row)
+                    wrapping += read and row >= n
+    assert wrapping > 0   # what a load of a tile without keys would read
 
 
 def test_kernels_fit_their_launches():
