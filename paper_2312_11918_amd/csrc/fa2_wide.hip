@@ -6,8 +6,8 @@
 // as copies of the last key: their columns of S are masked; a tile without any key is not asked for, see wide_staged_tile), and what
 // the epilogue derives from the lane is not kept through the loop.  256 registers, no scratch.  Without the mask the bits are those
 // of the 128-row shape; under it that one takes the row maximum on every one of its last tiles, this one only on those that the
-// diagonal crosses, so where a reference point moves there the last bits differ.  3.5 % at B8 H16 N2047 (258 -> 249 us, 1058 -> 1096
-// TFLOP/s: the clock under N(0,1) operands bounds it from there, as on whole tiles), 5 % under the mask, 7 % at N = 511 (see
+// diagonal crosses, so where a reference point moves there the last bits differ.  4 % at B8 H16 N2047 (271 -> 261 us, 1022 -> 1066
+// TFLOP/s: the clock under N(0,1) operands bounds it from there, as on whole tiles), 6 % under the mask, 9 % at N = 511 (see
 // fa2_wide_plan.h).
 #include "fa2_wide_plan.h"
 #include "fa2_tile_kernel.h"

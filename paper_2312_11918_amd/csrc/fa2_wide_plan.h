@@ -7,11 +7,11 @@ namespace fa2 {
 
 // d = 128.  The 256-row shape gains where it pads no more than the 128-row one, rows or keys, and where its Q tiles (under the mask
 // pairs of them, all complete) fill whole rounds of the CUs, so that one workgroup per CU takes a tile of every round over one
-// running K/V stream.  us, 128 rows / 256 rows: B8 H16 N2047 258 / 249, N2000 252 / 244, B4 H16 N4095 487 / 473, B16 H16 N1000 146 / 141,
-// B32 H16 N511 94.8 / 88.4, B8 H16 Nq2047 Nk3000 365 / 355, B16 H16 Nq2040 Nk255 112 / 105; causal B8 H16 N2047 161 / 153, B16 H16 N1000
-// 102 / 97, B32 H16 N500 78.7 / 77.2, B1 H16 N8100 251 / 242.  More padding: N1900 233 / 235, B16 H24 N640 96 / 130.  Rounds that are not
+// running K/V stream.  us, 128 rows / 256 rows: B8 H16 N2047 271 / 261, N2000 267 / 257, B4 H16 N4095 516 / 499, B16 H16 N1000 151 / 141,
+// B32 H16 N511 96.9 / 88.7, B8 H16 Nq2047 Nk3000 390 / 378, B16 H16 Nq2040 Nk255 112 / 104; causal B8 H16 N2047 166 / 156, B16 H16 N1000
+// 107 / 99, B32 H16 N500 77.9 / 75.4, B1 H16 N8100 267 / 258.  More padding: N1900 233 / 235, B16 H24 N640 96 / 130.  Rounds that are not
 // whole: B3 H16 N2000 (1.5) 102 / 107, B21 H16 N2040 (10.5) 634 / 647, causal B8 H16 N1500 (1.5) 98.6 / 110.  One tile per head: B64 H16 N250
-// 66.5 / 68.8.  A single round of short sequences: B8 H16 Nq500 Nk5000 156 / 157 (of long ones: B2 H16 N2000 65.7 / 64.2).
+// 66.5 / 68.8.  A single round of short sequences: B8 H16 Nq500 Nk5000 156 / 157 (of long ones: B2 H16 N2000 69.8 / 68.2).
 // Whole rounds are few of all problems, those of powers of two in B H.
 inline bool wide_accepts(int B, int H, int Nq, int Nk, int d, bool causal) {
   if (d != 128 || Nq <= 256 || (Nq == Nk && Nq % 256 == 0)) return false;   // (whole square tiles: fa2_fwd.hip)
