@@ -55,14 +55,14 @@ bool calls_are_seen() {
          at::getStepCallbacksUnlessEmpty(at::RecordScope::FUNCTION).has_value();
 }
 
-at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, c10::Device device) {
-  if (calls_are_seen()) return at::empty(sizes, at::TensorOptions().dtype(type).device(device));
+at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, c10::Device device, bool seen) {
+  if (seen) return at::empty(sizes, at::TensorOptions().dtype(type).device(device));
   return at::Tensor(at::detail::empty_cuda(sizes, type, device, std::nullopt));
 }
 
 // ... with the strides of t too: those of sizes of one may be any
-at::Tensor empty_as(const at::Tensor& t) {
-  if (calls_are_seen()) return at::empty_like(t);
+at::Tensor empty_as(const at::Tensor& t, bool seen) {
+  if (seen) return at::empty_like(t);
   return at::Tensor(at::detail::empty_strided_cuda(t.sizes(), t.strides(), t.scalar_type(), t.device()));
 }
 
@@ -121,13 +121,14 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   {
     // (an allocation waits for the driver at times, a launch where the queue is full)
     const WithoutGil released;
-    if (!out.defined()) out = empty_as(q);
-    if (return_lse && !lse.defined()) lse = empty({B, H, Nq}, at::kFloat, device);
+    const bool seen = calls_are_seen();
+    if (!out.defined()) out = empty_as(q, seen);
+    if (return_lse && !lse.defined()) lse = empty({B, H, Nq}, at::kFloat, device, seen);
     // Scratch of the launch stream: dropped on return, its memory is handed out again only behind this call's kernels.  Without
     // it the call still runs, its keys unsplit.
     if (bytes != 0) {
       try {
-        workspace = empty({(int64_t)bytes}, at::kByte, device);
+        workspace = empty({(int64_t)bytes}, at::kByte, device, seen);
       } catch (const c10::OutOfMemoryError&) {
       }
     }
